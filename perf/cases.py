@@ -1,0 +1,503 @@
+"""Workloads of the simulation library: inputs, one pass of each, and its value in 64 bits.
+
+A case is a plain dict; ``prepare`` builds what a program holds before the
+call (a context with its particles, a network and its rows), ``run`` makes one
+pass through the public entry points, ``exact`` computes what that pass
+returns with plain torch in FP64.  A simulation's pass is one tick of a
+program: advance by a number of substeps (or a frame), then read the particles
+back, as a renderer or a coupled solver does.  A pass moves the state on, so
+the passes of one state are consecutive ticks of one run.
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_2111_00699_amd import mpm, scenes
+
+MATERIALS = {"jelly": scenes.JELLY, "snow": scenes.SNOW, "water": scenes.WATER, "sand": scenes.SAND}
+WALLS = {"jelly": "sticky", "snow": "separate", "water": "separate", "sand": "slip"}
+GRAVITY = (0.0, -9.8, 0.0)
+TICK = 1.0 / 240.0  # four physics ticks per 1/60 s frame
+
+
+def listed():
+    return [
+        # the smallest call: one substep of a small body, read back at once (a solver coupled substep by substep)
+        {"name": "jelly_1.7k_1", "kind": "sim", "mat": "jelly", "n": 64, "shape": "box", "cells": 6, "steps": 1},
+        # the jelly cube of the parity scene (32,768 particles, 64^3), one 240 Hz tick
+        {"name": "jelly_32k", "kind": "sim", "mat": "jelly", "n": 64, "shape": "box", "cells": 16, "steps": 42},
+        # Sand Blocks, 4 boxes of 12^3 cells (55,296 particles, 128^3), one 1/48 s frame
+        {"name": "sand_55k", "kind": "sim", "mat": "sand", "n": 128, "shape": "blocks4", "cells": 12, "steps": 36},
+        # Sand Blocks, 4 boxes of 46^3 cells (3.1M particles, 128^3), one 1/48 s frame
+        {"name": "sand_3.1m", "kind": "sim", "mat": "sand", "n": 128, "shape": "blocks4", "cells": 46, "steps": 36},
+        # Sand Blocks, 16 boxes of 46^3 cells (12.5M particles, 256^3): the largest scene, a quarter of its frame
+        {"name": "sand_12.5m", "kind": "sim", "mat": "sand", "n": 256, "shape": "blocks16", "cells": 46, "steps": 18},
+        # the snow scene: 12 spheres in 256^3 (about 1.3M particles), half a 240 Hz tick
+        {"name": "snow_1.3m", "kind": "sim", "mat": "snow", "n": 256, "shape": "spheres", "cells": 14, "steps": 42},
+        # the fountain's pool and jet (about 143K particles, 128^3): a rebuild per tick, as emission forces one
+        {"name": "water_143k_rebuild", "kind": "sim", "mat": "water", "n": 128, "shape": "fountain", "cells": 64,
+         "steps": 42, "rebuild": True},
+        # the same with the paper's integrator: ASFLIP and the automatic time step, one 1/60 s frame
+        {"name": "water_143k_asflip", "kind": "asflip", "mat": "water", "n": 128, "shape": "fountain", "cells": 64},
+        # 64 small uneven scenes in one context, frames recorded as graphs, one 240 Hz tick of all of them
+        {"name": "batch_64", "kind": "batch", "scenes": 64, "most": 65536, "layout": 3},
+        # the network over a scene's worth of particles, in BF16 on the matrix cores (a ragged row count)
+        {"name": "net_forward_1.28m", "kind": "forward", "rows": 1280602, "precision": 1},
+        # training the network as the benchmark does: minibatches of 16,384 drawn from sampled pairs
+        {"name": "net_train_16k", "kind": "train", "rows": 2000003, "batch": 16384, "steps": 64},
+        # the normalisation of a whole training set (about 10.9M pairs)
+        {"name": "net_fit_norm_10.9m", "kind": "norm", "rows": 10939056},
+    ]
+
+
+def draw(rng):
+    def log(lo, hi):
+        return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+    what = rng.choice(["jelly", "sand", "sand", "snow", "snow", "water", "asflip", "batch", "forward", "train", "norm"])
+    if what == "jelly":  # 512 to 64K particles
+        return {"kind": "sim", "mat": "jelly", "n": 64, "shape": "box", "cells": log(4, 20), "steps": log(1, 42)}
+    if what == "sand":  # 16K to 3.1M particles
+        return {"kind": "sim", "mat": "sand", "n": 128, "shape": "blocks4", "cells": log(8, 46), "steps": 36}
+    if what == "snow":  # 25K to 1.3M particles
+        return {"kind": "sim", "mat": "snow", "n": 256, "shape": "spheres", "cells": log(4, 14), "steps": log(4, 42)}
+    if what == "water":  # 20K to 140K particles
+        return {"kind": "sim", "mat": "water", "n": 128, "shape": "fountain", "cells": log(24, 64),
+                "steps": log(4, 42), "rebuild": rng.random() < 0.5}
+    if what == "asflip":
+        return {"kind": "asflip", "mat": "water", "n": 128, "shape": "fountain", "cells": log(24, 64)}
+    if what == "batch":
+        return {"kind": "batch", "scenes": log(4, 64), "most": log(8192, 65536), "layout": rng.randrange(1, 1000)}
+    if what == "forward":
+        return {"kind": "forward", "rows": log(100, 1280602), "precision": rng.choice([1, 1, 0])}
+    if what == "train":
+        return {"kind": "train", "rows": log(20000, 2000003), "batch": log(1024, 16384), "steps": log(16, 64)}
+    return {"kind": "norm", "rows": log(1000, 10939056)}
+
+
+# ------------------------------------------------------------------ inputs
+def _generator(seed, stream=0):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(int(seed) * 1000003 + stream)
+    return g
+
+
+def _box(lo, edge):
+    """The cells of the box [lo, lo + edge) as (K, 3) integers."""
+    r = [torch.arange(lo[a], lo[a] + edge[a], device="cuda") for a in range(3)]
+    return torch.cartesian_prod(*r).reshape(-1, 3)
+
+
+def _cells(case):
+    """The cells a scene's particles start in (8 particles each); a property of the case, not of the seed."""
+    n, l, shape = case["n"], case["cells"], case["shape"]
+    if shape == "box":
+        return _box([(n - l) // 2] * 3, [l] * 3)
+    if shape in ("blocks4", "blocks16"):
+        side = 2 if shape == "blocks4" else 4
+        start = (n - (side * l + 2 * (side - 1))) // 2
+        return torch.cat([_box([start + i * (l + 2), n // 8, start + j * (l + 2)], [l] * 3)
+                          for j in range(side) for i in range(side)])
+    if shape == "spheres":  # twelve spheres of radius 0.6 l to 1.4 l cells, apart, in the middle of the box
+        u = scenes.uniform(1, 12, 100)
+        radius = np.sort(l * (0.6 + 0.8 * u))[::-1] * (n / 256.0)
+        at, k = [], 0
+        while len(at) < 12:
+            c = n * (np.array([0.15, 0.25, 0.15]) + np.array([0.7, 0.6, 0.7]) * scenes.uniform(1, 3, 1000 + k))
+            k += 1
+            r = radius[len(at)]
+            if all(np.linalg.norm(c - d) >= r + s + 2 for d, s in zip(at, radius)):
+                at.append(c)
+        out = []
+        for c, r in zip(at, radius):
+            lo = np.floor(c - r).astype(int)
+            cells = _box(lo.tolist(), [int(2 * r) + 3] * 3)
+            d = cells.double() + 0.5 - torch.tensor(c, device="cuda")
+            out.append(cells[(d * d).sum(1) <= r * r])
+        return torch.cat(out)
+    assert shape == "fountain"  # a pool of l x 3 x l cells and the jet above the inlet
+    pool = _box([(n - l) // 2, 3, (n - l) // 2], [l, 3, l])
+    r = 0.05 * n
+    jet = _box([int(0.5 * n - r) - 1, int(0.15 * n), int(0.5 * n - r) - 1], [int(2 * r) + 3, int(0.35 * n), int(2 * r) + 3])
+    d = jet.double() + 0.5 - 0.5 * n
+    return torch.cat([pool, jet[d[:, 0] ** 2 + d[:, 2] ** 2 <= r * r]])
+
+
+def _particles(cells, n, mat, seed, stream=0):
+    """Particles under way: stratified positions, a bulk motion with small-scale velocities on top, a strained material."""
+    g = _generator(seed, stream)
+    K = cells.shape[0]
+    sub = torch.cartesian_prod(*[torch.arange(2, device="cuda")] * 3).double()
+    u = torch.rand((K, 8, 3), generator=g, device="cuda", dtype=torch.float64)
+    x = (cells[:, None, :].double() + 0.5 * (sub[None] + u)) / n
+    x = x.reshape(-1, 3).T.float().contiguous()
+    N = x.shape[1]
+
+    def rand(rows, lo, hi):
+        return lo + (hi - lo) * torch.rand((rows, N), generator=g, device="cuda")
+
+    v = rand(3, -0.25, 0.25)
+    v[1] -= 0.5
+    st = {"x": x, "v": v, "C": rand(9, -3.0, 3.0), "F": rand(9, -0.01, 0.01)}
+    st["F"][[0, 4, 8]] += 1.0
+    lo, hi = {"jelly": (1.0, 1.0), "snow": (0.97, 1.03), "water": (0.99, 1.01), "sand": (1.0, 1.5)}[mat]
+    st["s"] = rand(1, lo, hi).reshape(-1)
+    return st
+
+
+def _time_step(mat, n):
+    """(time step, frame): the materials' steps at the grids they are used on, scaled to the grid."""
+    if mat == "sand":
+        return (1.0 / 48.0) / (36 * n // 128), 1.0 / 48.0
+    ref, at = {"jelly": (1e-4, 64), "snow": (5e-5, 256), "water": (1e-4, 128)}[mat]
+    return scenes.frame_substeps(ref * at / n)[1], scenes.FRAME
+
+
+def _batch_layout(case):
+    """The scenes of a batch: cubes of 2,048 to `most` particles of jelly, snow or water."""
+    out = []
+    for k in range(case["scenes"]):
+        u = scenes.uniform(case["layout"], 3, stream=k)
+        n = (64, 128)[min(int(u[0] * 2), 1)]
+        N = math.exp(math.log(2048) + u[1] * math.log(case["most"] / 2048))
+        mat = ("jelly", "snow", "water")[min(int(u[2] * 3), 2)]
+        out.append((n, mat, min(max(2, round((N / 8) ** (1 / 3))), n // 2 - 6)))
+    return out
+
+
+def _network(seed, rows):
+    """Rows of features and targets of the snow map, and starting parameters of the network."""
+    g = _generator(seed, 7)
+
+    def rand(shape, lo, hi):
+        return lo + (hi - lo) * torch.rand(shape, generator=g, device="cuda", dtype=torch.float64)
+
+    m = scenes.SNOW
+    s = (1.0 + rand((rows, 3), -0.02, 0.02)).sort(dim=1, descending=True).values
+    jp = rand((rows,), 0.85, 1.1)
+    sn = s.clamp(1 - m["theta_c"], 1 + m["theta_s"])
+    J, Jn = s.prod(1), sn.prod(1)
+    jn = jp * J / Jn
+    h, hn = torch.exp(m["xi"] * (1 - jp)), torch.exp(m["xi"] * (1 - jn))
+    mu, la = 1 / (2 * (1 + m["nu"])), m["nu"] / ((1 + m["nu"]) * (1 - 2 * m["nu"]))
+    tau = 2 * mu * hn[:, None] * (sn - 1) * sn + (la * hn * (Jn - 1) * Jn)[:, None]
+    one = torch.ones_like(jp)
+    dt = rand((rows,), 0.5, 1.5)
+    X = torch.cat([s, s.log(), torch.stack([jp, jp.log(), h, dt, J, one], 1)], 1).float()
+    T = torch.cat([sn, (sn / s).log(), tau, torch.stack([jn / jp, hn, Jn], 1)], 1).float()
+    theta = torch.tensor(scenes.mlp_init(4 + int(seed) % 97), device="cuda")
+    return X.contiguous(), T.contiguous(), theta
+
+
+def _norm64(X, T):
+    out = []
+    for A in (X.double(), T.double()):
+        out += [A.mean(0), A.var(0, unbiased=False).sqrt().clamp(min=1e-6)]
+    return torch.cat(out)
+
+
+def prepare(case, seed):
+    kind = case["kind"]
+    if kind in ("sim", "asflip"):
+        n, mat = case["n"], case["mat"]
+        st = _particles(_cells(case), n, mat, seed)
+        dt, frame = _time_step(mat, n)
+        sim = mpm.Sim(n, dt, bc=WALLS[mat], gravity=GRAVITY, capacity=2 * st["x"].shape[1])
+        sim.add_particles(MATERIALS[mat], st["x"], v=st["v"], C=st["C"], F=st["F"], s=st["s"])
+        if kind == "asflip":
+            sim.set_transfer(0.95, 0.0, 1.0)
+            sim.set_auto_dt(0.3, 1e-3)
+        sim.synchronize()
+        return {"case": case, "sim": sim, "frame": frame}
+    if kind == "batch":
+        layout = _batch_layout(case)
+        parts = [_particles(_box([(n - c) // 2, int(0.4 * n), (n - c) // 2], [c] * 3), n, mat, seed, 100 + k)
+                 for k, (n, mat, c) in enumerate(layout)]
+        desc = [dict(n=n, dt=_time_step(mat, n)[0], bc=WALLS[mat]) for n, mat, _ in layout]
+        torch.cuda.synchronize()
+        sim = mpm.Sim(64, 1e-4, gravity=GRAVITY, capacity=2 * sum(p["x"].shape[1] for p in parts),
+                      flags=mpm.FLAG_FRAME_GRAPHS, stream=torch.cuda.Stream(), scenes=desc)
+        for k, ((n, mat, _), st) in enumerate(zip(layout, parts)):
+            sim.add_particles(MATERIALS[mat], st["x"], v=st["v"], C=st["C"], F=st["F"], s=st["s"], scene=k)
+        sim.synchronize()
+        return {"case": case, "sim": sim}
+    X, T, theta = _network(seed, case["rows"])
+    net = mpm.Surrogate()
+    net.set(theta, None if kind == "norm" else _norm64(X, T).float())
+    return {"case": case, "net": net, "X": X, "T": T, "seed": int(seed)}
+
+
+def _returned(case, particles):
+    """What a tick hands on: the state.  C, a difference of neighbouring node velocities times 4 n, is part of it as
+    long as the small-scale motion lasts; once that has been damped (a few substeps) C is the 32-bit rounding of a
+    velocity 4 n times enlarged, and F, which integrates it, stands for it."""
+    return {k: t for k, t in particles.items() if k != "C" or case.get("steps", 99) <= 4}
+
+
+def run(state):
+    case = state["case"]
+    kind = case["kind"]
+    if kind == "sim":
+        if case.get("rebuild"):
+            state["sim"].rebuild()
+        state["sim"].substep(case["steps"])
+        return _returned(case, state["sim"].read_particles())
+    if kind == "asflip":
+        state["sim"].frame(state["frame"])
+        return _returned(case, state["sim"].read_particles())
+    if kind == "batch":
+        sim = state["sim"]
+        sim.frame(TICK)
+        got = [sim.read_particles(scene=k) for k in range(case["scenes"])]
+        return {f: torch.cat([p[f] for p in got], dim=-1) for f in ("x", "v", "F", "s")}
+    net = state["net"]
+    if kind == "forward":
+        return net.forward(state["X"], precision=case["precision"])
+    if kind == "train":
+        losses = net.train(state["X"], state["T"], steps=case["steps"], batch=case["batch"], lr=1e-3, seed=state["seed"])
+        return {"losses": losses, "theta": net.get()[0]}
+    net.fit_norm(state["X"], state["T"])
+    return net.get()[1]
+
+
+def work(case):
+    kind = case["kind"]
+    if kind in ("sim", "asflip", "batch"):
+        if kind == "batch":
+            todo = [(mat, 8 * c ** 3, math.ceil(TICK / _time_step(mat, n)[0] - 1e-4)) for n, mat, c in _batch_layout(case)]
+        elif kind == "asflip":  # about 44 substeps a frame
+            todo = [(case["mat"], 8 * _cells(case).shape[0], 44)]
+        else:
+            todo = [(case["mat"], 8 * _cells(case).shape[0], case["steps"])]
+        total = {"bytes": 0.0, "flops": 0.0}
+        for mat, N, steps in todo:
+            # a substep reads and writes position and strain (with ASFLIP velocity and its gradient too); the
+            # velocities of the last one and the read-back move the whole state once more
+            state = {"jelly": 48, "snow": 52, "water": 16, "sand": 52}[mat] + (48 if kind == "asflip" else 0)
+            total["bytes"] += N * (2 * state * steps + 2 * 100)
+            # 27 nodes: 4 channels out of the affine momentum (14 flops), 3 in and their gradient (12); the material
+            total["flops"] += N * steps * (27 * 26 + {"jelly": 600, "snow": 700, "water": 60, "sand": 700}[mat])
+        return total
+    rows = case["rows"]
+    per = 2 * (12 * 64 + 64 * 64 + 64 * 12)
+    if kind == "forward":
+        return {"bytes": 96.0 * rows + 4 * 5772, "flops": float(per * rows)}
+    if kind == "train":  # forward, and backward without the inputs' gradient
+        return {"bytes": case["steps"] * (96.0 * case["batch"] + 6 * 4 * 5772),
+                "flops": case["steps"] * case["batch"] * (2.0 * per + 2 * (64 * 64 + 64 * 12))}
+    return {"bytes": 96.0 * rows, "flops": 24.0 * 4 * rows}
+
+
+# ------------------------------------------------------------------ in 64 bits
+def _constants(mat):
+    """A material's constants as the library holds them (32-bit values)."""
+    return {k: float(np.float32(v)) for k, v in MATERIALS[mat].items() if k != "kind"}
+
+
+def _matmul(A, B):  # (9, N) times (9, N), entry (a, b) at 3 a + b
+    return torch.stack([sum(A[3 * a + k] * B[3 * k + b] for k in range(3)) for a in range(3) for b in range(3)])
+
+
+def _det(A):
+    return (A[0] * (A[4] * A[8] - A[5] * A[7]) - A[1] * (A[3] * A[8] - A[5] * A[6]) +
+            A[2] * (A[3] * A[7] - A[4] * A[6]))
+
+
+def _principal(F):
+    """Eigenvalues of F F^T and its eigenvectors (columns of U), by cyclic Jacobi rotations."""
+    b = [[sum(F[3 * i + k] * F[3 * j + k] for k in range(3)) for j in range(3)] for i in range(3)]
+    U = [[torch.ones_like(F[0]) if i == j else torch.zeros_like(F[0]) for j in range(3)] for i in range(3)]
+    for _ in range(6):
+        for p, q in ((0, 1), (0, 2), (1, 2)):
+            d = b[q][q] - b[p][p]
+            off = 2 * b[p][q]
+            den = d.abs() + torch.sqrt(d * d + off * off)
+            t = torch.where(den > 0, torch.where(d >= 0, off, -off) / den.clamp(min=1e-300), torch.zeros_like(d))
+            c = torch.rsqrt(1 + t * t)
+            s = t * c
+            for i in range(3):
+                b[i][p], b[i][q] = c * b[i][p] - s * b[i][q], s * b[i][p] + c * b[i][q]
+                U[i][p], U[i][q] = c * U[i][p] - s * U[i][q], s * U[i][p] + c * U[i][q]
+            for i in range(3):
+                b[p][i], b[q][i] = c * b[p][i] - s * b[q][i], s * b[p][i] + c * b[q][i]
+    sig = [b[k][k].clamp(min=0).sqrt() for k in range(3)]
+    least = torch.minimum(torch.minimum(sig[0], sig[1]), sig[2])
+    flipped = _det(F) < 0
+    return U, [torch.where(flipped & (x == least), -x, x) for x in sig]
+
+
+def _from_principal(U, d):  # U diag(d) U^T
+    return torch.stack([sum(U[a][k] * d[k] * U[b][k] for k in range(3)) for a in range(3) for b in range(3)])
+
+
+def _stress(mat, m, F, s):
+    if mat == "water":
+        p = m["bulk"] * (s - 1) * s
+        z = torch.zeros_like(p)
+        return torch.stack([p if k % 4 == 0 else z for k in range(9)])
+    mu, la = m["E"] / (2 * (1 + m["nu"])), m["E"] * m["nu"] / ((1 + m["nu"]) * (1 - 2 * m["nu"]))
+    U, sig = _principal(F)
+    if mat == "sand":
+        e = [x.abs().clamp(min=1e-6).log() for x in sig]
+        return _from_principal(U, [2 * mu * x + la * (e[0] + e[1] + e[2]) for x in e])
+    h = torch.exp(m["xi"] * (1 - s)) if mat == "snow" else 1.0
+    J = _det(F)
+    return _from_principal(U, [h * (2 * mu * (x - 1) * x + la * (J - 1) * J) for x in sig])
+
+
+def _update(mat, m, F, s, C, dt):
+    """The deformation after a substep: the trial gradient (I + dt C) F through the material's return map."""
+    G = dt * C
+    G[[0, 4, 8]] += 1.0
+    if mat == "water":
+        return F, s * _det(G)
+    F = _matmul(G, F)
+    if mat == "jelly":
+        return F, s
+    U, sig = _principal(F)
+    if mat == "snow":
+        new = [x.clamp(1 - m["theta_c"], 1 + m["theta_s"]) for x in sig]
+        s = s * (sig[0] * sig[1] * sig[2]) / (new[0] * new[1] * new[2])
+    else:
+        mu, la = m["E"] / (2 * (1 + m["nu"])), m["E"] * m["nu"] / ((1 + m["nu"]) * (1 - 2 * m["nu"]))
+        e = [x.abs().clamp(min=1e-6).log() for x in sig]
+        t = e[0] + e[1] + e[2]
+        d = [x - t / 3 for x in e]
+        nd = (d[0] ** 2 + d[1] ** 2 + d[2] ** 2).sqrt()
+        q = s - 1
+        rad = math.pi / 180
+        phi = m["h0"] * rad + (m["h1"] * rad * q - m["h3"] * rad) * torch.exp(-m["h2"] * q)
+        alpha = math.sqrt(2 / 3) * 2 * phi.sin() / (3 - phi.sin())
+        dg = nd + (3 * la + 2 * mu) / (2 * mu) * t * alpha
+        cone, zero = dg > 0, torch.zeros_like(t)
+        r = torch.where(cone, dg / nd.clamp(min=1e-300), zero)
+        new = [torch.where(t > 0, zero, x - r * y) for x, y in zip(e, d)]
+        gone = torch.where(t > 0, (e[0] ** 2 + e[1] ** 2 + e[2] ** 2).sqrt(), dg.clamp(min=0))
+        new = [torch.where(gone > 0, x.exp(), y) for x, y in zip(new, sig)]
+        s = s + gone
+    return F + _matmul(_from_principal(U, [a / b - 1 for a, b in zip(new, sig)]), F), s
+
+
+def _substeps(st, n, mat, dt, steps, flip=0.0, bmin=0.0, bmax=1.0):
+    """The definition of a substep on the dense grid, `steps` times, in FP64."""
+    m = _constants(mat)
+    dt = float(np.float32(dt))
+    x, v, C, F, s = (st[k].double() for k in ("x", "v", "C", "F", "s"))
+    dx, n1 = 1.0 / n, n + 1
+    vol = dx ** 3 / m["ppc"]
+    mass = m["rho"] * vol
+    g = torch.tensor([float(np.float32(a)) for a in GRAVITY], device=x.device, dtype=torch.float64)
+    i = torch.arange(n1, device=x.device)
+    low, high = i < 3, i > n - 3
+    side = [(1, -1, 1, 1), (1, 1, -1, 1), (1, 1, 1, -1)]
+    for _ in range(steps):
+        base = torch.floor(x * n - 0.5)
+        f = x * n - base
+        w = [0.5 * (1.5 - f) ** 2, 0.75 - (f - 1) ** 2, 0.5 * (f - 0.5) ** 2]
+        b = base.long()
+        A = mass * C - 4 * dt * vol / dx ** 2 * _stress(mat, m, F, s)
+
+        def nodes():
+            for ox in range(3):
+                for oy in range(3):
+                    for oz in range(3):
+                        d = (torch.tensor([[ox], [oy], [oz]], device=x.device) - f) * dx
+                        yield ((b[0] + ox) * n1 + b[1] + oy) * n1 + b[2] + oz, w[ox][0] * w[oy][1] * w[oz][2], d
+
+        grid = torch.zeros((n1 ** 3, 4), device=x.device, dtype=torch.float64)
+        for at, wt, d in nodes():
+            p = [mass * v[a] + sum(A[3 * a + k] * d[k] for k in range(3)) for a in range(3)]
+            grid.index_add_(0, at, torch.stack([wt * mass] + [wt * q for q in p], 1))
+        some = grid[:, :1] > 0
+        old = torch.where(some, grid[:, 1:] / torch.where(some, grid[:, :1], 1.0), 0.0)
+        u = torch.where(some, old + dt * g, 0.0).reshape(n1, n1, n1, 3)
+        at_low, at_high = [low.view(k[1:]) for k in side], [high.view(k[1:]) for k in side]
+        if WALLS[mat] == "sticky":
+            u[at_low[0] | at_high[0] | at_low[1] | at_high[1] | at_low[2] | at_high[2]] = 0.0
+        else:
+            for a in range(3):
+                if WALLS[mat] == "slip":
+                    hit = (at_low[a] | at_high[a]).expand(n1, n1, n1)
+                else:
+                    hit = (at_low[a] & (u[..., a] < 0)) | (at_high[a] & (u[..., a] > 0))
+                u[..., a] = torch.where(hit, 0.0, u[..., a])
+        u = u.reshape(-1, 3)
+        new, C = torch.zeros_like(v), torch.zeros_like(C)
+        before = torch.zeros_like(v)
+        for at, wt, d in nodes():
+            vi = u[at].T
+            new += wt * vi
+            C += torch.stack([wt * vi[a] * d[k] for a in range(3) for k in range(3)])
+            if flip > 0:
+                before += wt * old[at].T
+        C *= 4 / dx ** 2
+        moved = new
+        if flip > 0:
+            G = dt * C
+            G[[0, 4, 8]] += 1.0
+            J = _det(G) * (s if mat == "water" else 1.0)
+            fix = flip * (v - before)
+            moved = new + torch.where(J < 1, bmin, bmax) * fix
+            new = new + fix
+        x, v = x + dt * moved, new
+        F, s = _update(mat, m, F, s, C, dt)
+    return {"x": x, "v": v, "C": C, "F": F, "s": s}
+
+
+def _forward64(theta, norm, X):
+    W1, b1, W2, b2, W3, b3 = torch.split(theta, [768, 64, 4096, 64, 768, 12])
+    h0 = (X - norm[:12]) / norm[12:24]
+    h1 = torch.tanh(h0 @ W1.view(64, 12).T + b1)
+    h2 = torch.tanh(h1 @ W2.view(64, 64).T + b2)
+    return h0, h1, h2, h2 @ W3.view(12, 64).T + b3
+
+
+def _train64(theta, norm, X, T, steps, batch, seed, lr=1e-3):
+    lr, beta1, beta2, eps = (float(np.float32(a)) for a in (lr, 0.9, 0.999, 1e-8))
+    m, v, losses = torch.zeros_like(theta), torch.zeros_like(theta), []
+    for k in range(steps):
+        with np.errstate(over="ignore"):
+            z = (np.uint64(k) << np.uint64(32)) + np.arange(batch, dtype=np.uint64)
+            z = np.uint64(seed) + z * scenes.GOLDEN + scenes.GOLDEN
+            z = (z ^ (z >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
+            z = (z ^ (z >> np.uint64(27))) * np.uint64(0x94D049BB133111EB)
+            z ^= z >> np.uint64(31)
+        rows = torch.from_numpy((z % np.uint64(X.shape[0])).astype(np.int64)).to(X.device)
+        x, t = X[rows].double(), (T[rows].double() - norm[24:36]) / norm[36:]
+        h0, h1, h2, y = _forward64(theta, norm, x)
+        losses.append(0.5 * ((y - t) ** 2).sum() / batch)
+        d3 = (y - t) / batch
+        d2 = (d3 @ theta[4992:5760].view(12, 64)) * (1 - h2 * h2)
+        d1 = (d2 @ theta[832:4928].view(64, 64)) * (1 - h1 * h1)
+        g = torch.cat([(d1.T @ h0).reshape(-1), d1.sum(0), (d2.T @ h1).reshape(-1), d2.sum(0),
+                       (d3.T @ h2).reshape(-1), d3.sum(0)])
+        m, v = beta1 * m + (1 - beta1) * g, beta2 * v + (1 - beta2) * g * g
+        theta = theta - lr * (m / (1 - beta1 ** (k + 1))) / ((v / (1 - beta2 ** (k + 1))).sqrt() + eps)
+    return {"losses": torch.stack(losses), "theta": theta}
+
+
+def exact(case, seed):
+    kind = case["kind"]
+    if kind == "batch":  # many small scenes one after another: too long
+        return None
+    if kind in ("sim", "asflip"):
+        n, mat = case["n"], case["mat"]
+        st = _particles(_cells(case), n, mat, seed)
+        if kind == "sim":
+            got = _substeps(st, n, mat, _time_step(mat, n)[0], case["steps"])
+        else:
+            m, frame = _constants(mat), float(np.float32(_time_step(mat, n)[1]))
+            fastest = float(st["v"].double().pow(2).sum(0).sqrt().max())
+            dt = min(float(np.float32(1e-3)), float(np.float32(0.3)) / n /
+                     (fastest + float(np.float32(9.8)) * frame + math.sqrt(m["bulk"] / m["rho"])))
+            steps = max(1, math.ceil(frame / dt - 1e-9))
+            got = _substeps(st, n, mat, frame / steps, steps, float(np.float32(0.95)), 0.0, 1.0)
+        return _returned(case, got)
+    X, T, theta = _network(seed, case["rows"])
+    if kind == "norm":
+        return _norm64(X, T)
+    norm = _norm64(X, T).float().double()
+    if kind == "forward":
+        return _forward64(theta.double(), norm, X.double())[3] * norm[36:] + norm[24:36]
+    return _train64(theta.double(), norm, X, T, case["steps"], case["batch"], int(seed))
