@@ -33,8 +33,8 @@ def listed():
         {"name": "sand_3.1m", "kind": "sim", "mat": "sand", "n": 128, "shape": "blocks4", "cells": 46, "steps": 36},
         # Sand Blocks, 16 boxes of 46^3 cells (12.5M particles, 256^3): the largest scene, a quarter of its frame
         {"name": "sand_12.5m", "kind": "sim", "mat": "sand", "n": 256, "shape": "blocks16", "cells": 46, "steps": 18},
-        # the snow scene: 12 spheres in 256^3 (about 1.3M particles), half a 240 Hz tick
-        {"name": "snow_1.3m", "kind": "sim", "mat": "snow", "n": 256, "shape": "spheres", "cells": 14, "steps": 42},
+        # the snow scene: 12 spheres in 256^3 (about 1.4M particles), half a 240 Hz tick
+        {"name": "snow_1.4m", "kind": "sim", "mat": "snow", "n": 256, "shape": "spheres", "cells": 16, "steps": 42},
         # the fountain's pool and jet (about 143K particles, 128^3): a rebuild per tick, as emission forces one
         {"name": "water_143k_rebuild", "kind": "sim", "mat": "water", "n": 128, "shape": "fountain", "cells": 64,
          "steps": 42, "rebuild": True},
@@ -60,8 +60,8 @@ def draw(rng):
         return {"kind": "sim", "mat": "jelly", "n": 64, "shape": "box", "cells": log(4, 20), "steps": log(1, 42)}
     if what == "sand":  # 16K to 3.1M particles
         return {"kind": "sim", "mat": "sand", "n": 128, "shape": "blocks4", "cells": log(8, 46), "steps": 36}
-    if what == "snow":  # 25K to 1.3M particles
-        return {"kind": "sim", "mat": "snow", "n": 256, "shape": "spheres", "cells": log(4, 14), "steps": log(4, 42)}
+    if what == "snow":  # 22K to 1.4M particles
+        return {"kind": "sim", "mat": "snow", "n": 256, "shape": "spheres", "cells": log(4, 16), "steps": log(4, 42)}
     if what == "water":  # 20K to 140K particles
         return {"kind": "sim", "mat": "water", "n": 128, "shape": "fountain", "cells": log(24, 64),
                 "steps": log(4, 42), "rebuild": rng.random() < 0.5}
