@@ -594,7 +594,7 @@ int substep_one(mpm_ctx* c, int act) {
     if ((r = prof_begin(c, 1, &slot))) return r;
     enqueue_p2g(c->stream, p2g_launch(c), T, c->S[c->cur], c->cap, c->B.chunks, c->ctl, c->G, c->B.brick_state,
                 fused ? 1 : c->pending, parity, (c->cfg.flags & MPM_FLAG_P2G_GLOBAL_ATOMICS) ? 1 : 0, c->nbricks,
-                c->cfg.chunk, act, fused ? 1 : 0, c->ring_dev + rs, fb_limit(c));
+                c->cfg.chunk, act, fused ? 1 : 0, c->ring_dev + rs, fb_limit(c), c->any_flip ? 1 : 0);
     if ((r = prof_end(c, slot))) return r;
     if ((r = prof_begin(c, 2, &slot))) return r;
     enqueue_grid(c->stream, c->L, T, c->B, c->ctl, c->G, parity, c->nbricks, act, grid_separate(c));
@@ -645,7 +645,7 @@ int record_frame_graph(mpm_ctx* c, int cur, bool rebuild, float frame_dt, const 
         const bool fused = fuse && k > 0;
         enqueue_p2g(c->stream, p2g_launch(c), T, c->S[buf], c->cap, c->B.chunks, c->ctl, c->G, c->B.brick_state, 1,
                     parity, (c->cfg.flags & MPM_FLAG_P2G_GLOBAL_ATOMICS) ? 1 : 0, c->nbricks, c->cfg.chunk, act,
-                    fused ? 1 : 0, flag, fb_limit(c));
+                    fused ? 1 : 0, flag, fb_limit(c), c->any_flip ? 1 : 0);
         enqueue_grid(c->stream, c->L, T, c->B, c->ctl, c->G, parity, c->nbricks, act, grid_separate(c));
         if (!fuse)
             enqueue_g2p(c->stream, c->L, T, c->S[buf], c->cap, c->B.chunks, c->ctl, c->G, flag, lds_box, parity,

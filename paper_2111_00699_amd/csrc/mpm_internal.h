@@ -238,9 +238,10 @@ inline int chunk_threads(int chunk) { return chunk <= 128 ? 128 : chunk <= 256 ?
 // fused: the previous substep's G2P runs inside P2G (see k_p2g); host_flag
 // and fb_limit serve its free-zone request.  Only with the tile path and the
 // exact return map (T.sur_any == 0, global_atomics == 0).
+// f32: some scene takes ASFLIP (FP32 terms in the tile, see mpm_p2g.hip).
 void enqueue_p2g(hipStream_t st, const Launch& L, const Scenes& T, float* S, int64_t cap, const Chunk* chunks,
                  int* ctl, GridBuffers& G, int* brick_state, int pending, int parity, int global_atomics,
-                 int nbricks, int chunk, int act, int fused, int* host_flag, int fb_limit);
+                 int nbricks, int chunk, int act, int fused, int* host_flag, int fb_limit, int f32);
 int p2g_grid_size(int cus, int chunk);
 // Workgroups of `threads` threads that fit on one compute unit at once, from
 // the kernel's register and LDS use (gfx950: 512 VGPRs per lane and SIMD,
@@ -291,42 +292,87 @@ __device__ __forceinline__ uint32_t compact3(uint32_t v) {  // inverse of spread
     return v;
 }
 
-// One Jacobi rotation of a symmetric 3x3 in the (p,q) plane that zeroes a_pq;
-// r is the remaining index.  The rotation is accumulated into columns p, q of U.
-__device__ __forceinline__ void jacobi_rotate(float& app, float& aqq, float& apq, float& arp, float& arq, float& u0p,
-                                              float& u0q, float& u1p, float& u1q, float& u2p, float& u2q) {
+// The angle of the Jacobi rotation that zeroes the off-diagonal entry apq of a
+// symmetric matrix with entries of order one, as (cosine c, sine s, tangent
+// t).  The floor under the denominator replaces a branch for zero ones: below
+// it apq is under 1e-18 (its square no longer a normal number), t stays of
+// order one and t apq far below the rounding of the diagonal.
+__device__ __forceinline__ void jacobi_angle(float app, float aqq, float apq, float& c, float& s, float& t) {
     const float d = aqq - app;
     const float den = fabsf(d) + sqrtf(d * d + 4.0f * apq * apq);
-    const float t = den > 0.0f ? __fdividef(d >= 0.0f ? 2.0f * apq : -2.0f * apq, den) : 0.0f;
-    const float c = rsqrtf(1.0f + t * t);
-    const float s = t * c;
-    app -= t * apq;
-    aqq += t * apq;
-    apq = 0.0f;
-    const float rp = arp, rq = arq;
-    arp = c * rp - s * rq;
-    arq = s * rp + c * rq;
-    float a, b;
-    a = u0p; b = u0q; u0p = c * a - s * b; u0q = s * a + c * b;
-    a = u1p; b = u1q; u1p = c * a - s * b; u1q = s * a + c * b;
-    a = u2p; b = u2q; u2p = c * a - s * b; u2q = s * a + c * b;
+    t = __fdividef(d >= 0.0f ? 2.0f * apq : -2.0f * apq, fmaxf(den, 1e-18f));
+    c = rsqrtf(1.0f + t * t);
+    s = t * c;
+}
+
+// (p, q) <- (c p - s q, s p + c q)
+__device__ __forceinline__ void rotate(float c, float s, float& p, float& q) {
+    const float a = p, b = q;
+    p = c * a - s * b;
+    q = s * a + c * b;
 }
 
 // Eigen-decomposition of the symmetric b = [b00 b01 b02; . b11 b12; . . b22]
 // by cyclic Jacobi sweeps.  On return lam[k] are the eigenvalues and column k
-// of U (U[i*3+k]) the matching unit eigenvector.
+// of U (U[i*3+k]) the matching unit eigenvector.  Each rotation zeroes one
+// off-diagonal entry and rotates the other two, one of which the rotation
+// before it has zeroed (all but the very first): those products, and the
+// first sweep's with the identity, are not formed.
 __device__ __forceinline__ void eig_sym3(float b00, float b01, float b02, float b11, float b12, float b22, float U[9],
                                          float lam[3]) {
-    float u00 = 1, u01 = 0, u02 = 0, u10 = 0, u11 = 1, u12 = 0, u20 = 0, u21 = 0, u22 = 1;
+    float c, s, t;
+    // first sweep, U starting from the identity
+    jacobi_angle(b00, b11, b01, c, s, t);
+    b00 -= t * b01;
+    b11 += t * b01;
+    rotate(c, s, b02, b12);
+    float u00 = c, u01 = s, u10 = -s, u11 = c;
+    jacobi_angle(b00, b22, b02, c, s, t);
+    b00 -= t * b02;
+    b22 += t * b02;
+    b01 = -s * b12;  // the rotation zeroes b02; b01 was zero
+    b12 = c * b12;
+    float u02 = s * u00, u12 = s * u10, u20 = -s, u22 = c;
+    u00 = c * u00;
+    u10 = c * u10;
+    jacobi_angle(b11, b22, b12, c, s, t);
+    b11 -= t * b12;
+    b22 += t * b12;
+    b02 = s * b01;
+    b01 = c * b01;
+    rotate(c, s, u01, u02);
+    rotate(c, s, u11, u12);
+    float u21 = -s * u22;
+    u22 = c * u22;
 #pragma unroll
-    for (int sweep = 0; sweep < 3; ++sweep) {  // quadratic convergence: 3 sweeps reach FP32 rounding
-        // the third sweep only if some lane of the wave still has off-diagonal mass above
-        // FP32 rounding (|offdiag| > 1e-7 |diag|)
-        if (sweep == 2 && __all(b01 * b01 + b02 * b02 + b12 * b12 <= 1e-14f * (b00 * b00 + b11 * b11 + b22 * b22)))
-            break;
-        jacobi_rotate(b00, b11, b01, b02, b12, u00, u01, u10, u11, u20, u21);  // (0,1), r = 2
-        jacobi_rotate(b00, b22, b02, b01, b12, u00, u02, u10, u12, u20, u22);  // (0,2), r = 1
-        jacobi_rotate(b11, b22, b12, b01, b02, u01, u02, u11, u12, u21, u22);  // (1,2), r = 0
+    for (int sweep = 1; sweep < 3; ++sweep) {  // quadratic convergence: 3 sweeps reach FP32 rounding
+        // b12 is zero here.  The third sweep only if some lane of the wave still has off-diagonal
+        // mass above FP32 rounding (|offdiag| > 1e-7 |diag|)
+        if (sweep == 2 && __all(b01 * b01 + b02 * b02 <= 1e-14f * (b00 * b00 + b11 * b11 + b22 * b22))) break;
+        jacobi_angle(b00, b11, b01, c, s, t);
+        b00 -= t * b01;
+        b11 += t * b01;
+        b12 = s * b02;
+        b02 = c * b02;
+        rotate(c, s, u00, u01);
+        rotate(c, s, u10, u11);
+        rotate(c, s, u20, u21);
+        jacobi_angle(b00, b22, b02, c, s, t);
+        b00 -= t * b02;
+        b22 += t * b02;
+        b01 = -s * b12;
+        b12 = c * b12;
+        rotate(c, s, u00, u02);
+        rotate(c, s, u10, u12);
+        rotate(c, s, u20, u22);
+        jacobi_angle(b11, b22, b12, c, s, t);
+        b11 -= t * b12;
+        b22 += t * b12;
+        b02 = s * b01;
+        b01 = c * b01;
+        rotate(c, s, u01, u02);
+        rotate(c, s, u11, u12);
+        rotate(c, s, u21, u22);
     }
     lam[0] = b00; lam[1] = b11; lam[2] = b22;
     U[0] = u00; U[1] = u01; U[2] = u02;

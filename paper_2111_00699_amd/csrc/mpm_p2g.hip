@@ -46,16 +46,49 @@ constexpr int CT = 1024;  // LDS tile capacity in nodes (padded layout, below)
 
 // LDS tile layout: the padded node-box layout (pitch_row, pitch_plane in
 // mpm_kernels.h), four 64-bit fixed-point channels: the weight sum in units
-// of 2^-51 and the three momentum components in units of 2^-FRAC_M of the
+// of 2^-FRAC_W and the three momentum components in units of 2^-FRAC_M of the
 // chunk's momentum scale (below).  Integer adds are exact and
 // order-independent, and ds_add_u64 meets far fewer conflict cycles than
 // ds_add_f64 (a replay of late-frame snow stencils: 14 against 22 cycles per
 // wave instruction).
-constexpr float W_SCALE = 0x1p51f;  // weight units per 1: w <= 27/64, so w W_SCALE < 2^50
-constexpr int FRAC_M = 50;          // momentum: |w m| scaled below 2^50 per contribution
-// A contribution below this weight goes to the global FP32 accumulator
-// instead: a node that only such contributions reach would be resolved to
-// too few fixed-point units for its velocity (momentum / mass).
+//
+// A contribution becomes a fixed-point word in one FP64 multiplication: the
+// bits of a non-negative denormal k 2^-1074 are the integer k (and up to
+// 2^53, where the exponent field becomes 1, they go on counting), so a product
+// scaled into that range comes out rounded to the nearest unit, as a 64-bit
+// integer.  Momentum is made non-negative by adding the chunk's bound K to
+// it (w (m + K) instead of w m); the tile store takes K times the weight sum
+// off again.  FP64 keeps denormals in every build (the flush-to-zero of the
+// fast-math build is FP32's).  About 10 instructions per node and particle,
+// against 20 with FP32 products, a conversion, a rounding addition and a
+// subtraction of its bits per channel (and 24, with a branch per node, in the
+// 59% of the waves that tested every term for a tiny weight): VALU issue binds
+// this kernel at scenes of a million particles (84% busy before), the longest
+// workgroup at small ones.  Fused P2G before and after: 109.6 -> 101.6 us on
+// snow of 1.39M particles, 259 -> 244 us on sand of 3.1M, 16.5 -> 14.4 us on
+// jelly of 32K.
+constexpr int FRAC_W = 54;  // weight: w <= 27/64, below 2^53 units; 512 of them below 2^62
+constexpr int FRAC_M = 53;  // momentum: w (m + K) scaled below 2^53 units
+constexpr double DENORM_SPLIT = 0x1p-1000;  // the weights' share of the scale into the denormal range
+// A node whose weight sum in the tile is below this (2^-32) would be resolved
+// to too few units for its velocity (momentum / mass): the tile store lists
+// it, and its particles add to it again, in FP64 and unscaled.  The sum
+// decides, not the single contribution: about one particle in 70 has a
+// weight below 2^-32 somewhere in its stencil (59% of the waves), but only a
+// node at the very edge of a chunk's material has no other contribution.
+constexpr unsigned long long WEAK_SUM = 1ull << (FRAC_W - 32);
+
+// Contexts with an ASFLIP scene keep FP32 terms (F32 below): the products w
+// and w m are rounded to FP32, then to units of 2^-51 (weight) and 2^(em - 50)
+// (momentum) as two's complement words, and a term of weight below 2^-32
+// goes to the node's global accumulator.  ASFLIP's position share jumps where
+// a particle's volume change crosses 1, so any other rounding of a node
+// velocity sends some particles of a frame another way (of 142K fountain
+// particles about 60 in 44 substeps, J then off by up to 2e-3): there results
+// stay comparable from build to build only with the same rounding.  It costs
+// about 2 of that scene's 20 us per launch.
+constexpr float W_SCALE_F32 = 0x1p51f;
+constexpr int FRAC_M_F32 = 50;
 constexpr float TINY_W = 0x1p-32f;
 
 // Round-to-nearest integer of y (|y| < 2^51) as a 64-bit two's-complement
@@ -63,6 +96,8 @@ constexpr float TINY_W = 0x1p-32f;
 __device__ __forceinline__ unsigned long long fixed64(float y) {
     return (unsigned long long)(__double_as_longlong((double)y + 0x1.8p52) - 0x4338000000000000LL);
 }
+
+__device__ __forceinline__ float pick3(const float w[3], int o) { return o == 0 ? w[0] : o == 1 ? w[1] : w[2]; }
 
 // ------------------------------------------------ snow return map without SVD
 // Eigenvalues of the symmetric b = [b0 b1 b2; . b3 b4; . . b5] as
@@ -238,7 +273,7 @@ __device__ void snow_without_svd(const mlp::NetLds16* net, float* stage, const S
 // v, C and x; the particle's v and C are not stored (the G2P that brings the
 // state up to date before a read recomputes them).  vel, host_flag and
 // fb_limit serve that G2P.
-template <bool GLOBAL_ONLY, int NT, int SURM, bool FUSED>
+template <bool GLOBAL_ONLY, int NT, int SURM, bool FUSED, bool F32 = false>
 __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, const Chunk* __restrict__ chunks,
                                          int* __restrict__ ctl, float* __restrict__ acc,
                                          int* __restrict__ acc_dirty, float4* __restrict__ stage,
@@ -246,9 +281,14 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, con
                                          int* __restrict__ ovf, int parity, const Scenes& T, int pending,
                                          int nbricks, int act, const float4* __restrict__ vel,
                                          int* __restrict__ host_flag, int fb_limit) {
+    static_assert(!F32 || (!GLOBAL_ONLY && !FUSED), "FP32 terms: the separate tile path");
     static_assert(!FUSED || (!GLOBAL_ONLY && SURM == 0), "the fused G2P needs the LDS tile and the exact map");
     __shared__ __align__(16) double tq[GLOBAL_ONLY ? 1 : 4 * CT];
     __shared__ int red_i[7][NT / 64];
+    // weak nodes of the tile: their box coordinates, 5 bits an axis (a box spans at most 16 nodes:
+    // the reach of one 2x2x1 slab of blocks)
+    __shared__ unsigned short weak[GLOBAL_ONLY ? 1 : CT];
+    __shared__ int n_weak;
 #ifndef MPM_WEIGHTS_IN_LDS
 #define MPM_WEIGHTS_IN_LDS 0
 #endif
@@ -267,6 +307,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, con
     if constexpr (!GLOBAL_ONLY) {  // (workgroup-uniform: skipped by a workgroup without chunks)
         if (begin < end) {
             for (int t = threadIdx.x; t < 4 * CT; t += NT) tq[t] = 0.0;
+            if (threadIdx.x == 0) n_weak = 0;
             __syncthreads();
         }
     }
@@ -294,29 +335,26 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, con
         Stencil st;
         float q[3] = {0.f, 0.f, 0.f}, Ad[9];
         bool ok = false, in_zone = false;
-        float x[3] = {0.5f, 0.5f, 0.5f}, v[3] = {0.f, 0.f, 0.f}, C[9], F[9], s = 1.0f, tau[6];
+        // (lanes past the chunk's end load its first particle: no branch and no defaults)
+        float x[3], v[3] = {0.f, 0.f, 0.f}, C[9], F[9], s, tau[6];
 #pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            C[k] = 0.0f;
-            F[k] = (k % 4 == 0) ? 1.0f : 0.0f;
+        for (int a = 0; a < 3; ++a) x[a] = S[sidx(FX + a, p, cap)];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) C[k] = FUSED ? 0.0f : S[sidx(FC + k, p, cap)];
+        if (!FUSED) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) v[a] = S[sidx(FV + a, p, cap)];
         }
-        if (have) {
+        s = S[sidx(FS, p, cap)];
+        int B[3];  // the particle's block at the last rebuild (its free zone)
+        fsid_block(S[sidx(FSID, p, cap)], B);
+        if (M.kind != MPM_WATER) {
 #pragma unroll
-            for (int a = 0; a < 3; ++a) x[a] = S[sidx(FX + a, p, cap)];
-            if (!FUSED) {
+            for (int k = 0; k < 9; ++k) F[k] = S[sidx(FF + k, p, cap)];
+        } else {
 #pragma unroll
-                for (int a = 0; a < 3; ++a) v[a] = S[sidx(FV + a, p, cap)];
-#pragma unroll
-                for (int k = 0; k < 9; ++k) C[k] = S[sidx(FC + k, p, cap)];
-            }
-            s = S[sidx(FS, p, cap)];
-            if (M.kind != MPM_WATER) {
-#pragma unroll
-                for (int k = 0; k < 9; ++k) F[k] = S[sidx(FF + k, p, cap)];
-            }
+            for (int k = 0; k < 9; ++k) F[k] = 0.0f;  // not used
         }
-        int B[3] = {0, 0, 0};  // the particle's block at the last rebuild (its free zone)
-        if (have) fsid_block(S[sidx(FSID, p, cap)], B);
         int ng = 0, ngs = 0;  // fused G2P: nodes of the previous box, and the LDS float4 they span
         if constexpr (FUSED) {
             const int4 bb = box[c];  // this chunk's tile box of the previous substep
@@ -397,20 +435,21 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, con
         // ---- the box of the in-zone stencils of the chunk
         int lo[3] = {0, 0, 0}, ext[3] = {0, 0, 0};
         int nt = 0, off = 0, R = 4, Q = 8;  // tight node count, staging offset, LDS pitches
-        float m_scale = 1.0f, m_unit = 1.0f;  // momentum fixed-point scale of the chunk and its inverse
+        float m_bound = 0.0f;  // K, above every |m| of the chunk
+        int em = 0;            // 27/64 (m + K) < 2^em: momentum units are 2^(em - FRAC_M)
         if (GLOBAL_ONLY && tid == 0) box[c] = make_int4(0, 0, 0, 0);
         if (!GLOBAL_ONLY) {
-            const bool tiled = have && in_zone;
+            const bool in_tile = have && in_zone;
             int mn[3], mx[3];
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                mn[a] = wave_min(tiled ? st.base[a] : INT_MAX);
-                mx[a] = wave_max(tiled ? st.base[a] + 2 : INT_MIN);
+                mn[a] = wave_min(in_tile ? st.base[a] : INT_MAX);
+                mx[a] = wave_max(in_tile ? st.base[a] + 2 : INT_MIN);
             }
             // bound on |q_a + Ad_a . o| over the stencil (o in {0,1,2}^3), the momentum a tiled
             // particle sends to a node before its weight (non-negative: ordered as an int)
             float mb = 0.0f;
-            if (tiled) {
+            if (in_tile) {
 #pragma unroll
                 for (int a = 0; a < 3; ++a)
                     mb = fmaxf(mb, fabsf(q[a]) + 2.0f * (fabsf(Ad[3 * a]) + fabsf(Ad[3 * a + 1]) + fabsf(Ad[3 * a + 2])));
@@ -444,15 +483,11 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, con
                 }
                 mbk = max(mbk, red_i[6][k]);
             }
-            // the chunk's momentum scale 2^(FRAC_M - em): every contribution |w m| < 27/64 * bound
-            // < 2^em stays below 2^FRAC_M units
-            {
-                int em = 0;
-                (void)frexpf(0.421875f * __int_as_float(mbk), &em);
-                em = min(max(em, -70), 77);
-                m_scale = ldexpf(1.0f, FRAC_M - em);
-                m_unit = ldexpf(1.0f, em - FRAC_M);
-            }
+            // the chunk's momentum bound, above the rounding of the particles' own bounds and of m, and
+            // its scale: every contribution w (m + K) <= 27/64 2 K < 2^em
+            m_bound = 1.0001f * __int_as_float(mbk);
+            (void)frexpf(F32 ? 0.421875f * __int_as_float(mbk) : 0.84375f * m_bound, &em);
+            em = min(max(em, -70), 77);
             if (hi[0] >= lo[0]) {
 #pragma unroll
                 for (int a = 0; a < 3; ++a) ext[a] = hi[a] - lo[a] + 1;
@@ -489,28 +524,25 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, con
             for (int k = 0; k < 9; ++k) st.w[k / 3][k % 3] = wpark[k * NT + tid];
         }
 #endif
-        // Tile lanes whose stencil holds a weight below TINY_W send those
-        // contributions to the global accumulators instead; the smallest of a
-        // stencil's 27 weights is the product of its per-axis minima.  The
-        // per-node test is only compiled into the pass of waves that have
-        // such a lane (rare: a coordinate within 2^-11 dx of a cell edge).
-        bool any_tiny = false;
-        if (!GLOBAL_ONLY) {
+        const bool tiled = !GLOBAL_ONLY && have && ok && in_zone && nt > 0;
+        int tb = 0;  // tile index of the stencil's first node
+        if constexpr (F32) {
+            // Lanes whose stencil holds a weight below TINY_W; the smallest of a stencil's 27 weights is
+            // the product of its per-axis minima.
             float wmin = 1.0f;
 #pragma unroll
             for (int a = 0; a < 3; ++a) wmin *= fminf(fminf(st.w[a][0], st.w[a][1]), st.w[a][2]);
-            any_tiny = __any(have && ok && in_zone && nt > 0 && wmin < TINY_W);
-        }
-        if (have && ok) {
-            if (!GLOBAL_ONLY && in_zone && nt > 0) {
-                const int tb = (st.base[0] - lo[0]) + R * (st.base[1] - lo[1]) + Q * (st.base[2] - lo[2]);
+            const bool any_tiny = __any(tiled && wmin < TINY_W);
+            if (tiled) {
+                tb = (st.base[0] - lo[0]) + R * (st.base[1] - lo[1]) + Q * (st.base[2] - lo[2]);
                 unsigned long long* tu = reinterpret_cast<unsigned long long*>(tq);
+                const float m_scale = ldexpf(1.0f, FRAC_M_F32 - em), m_unit = ldexpf(1.0f, em - FRAC_M_F32);
                 float qs[3], As[9];  // in momentum units (exact: a power-of-two scale)
 #pragma unroll
                 for (int a = 0; a < 3; ++a) qs[a] = q[a] * m_scale;
 #pragma unroll
                 for (int k = 0; k < 9; ++k) As[k] = Ad[k] * m_scale;
-                auto scatter = [&](auto check) {
+                auto scatter = [&](auto check) {  // (the test of each term only in waves that need it)
                     constexpr bool CHECK = decltype(check)::value;
 #pragma unroll
                     for (int o2 = 0; o2 < 3; ++o2)
@@ -526,7 +558,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, con
                                 const float w = wyz * st.w[0][o0];
                                 const int t = row + o0;
                                 if (!CHECK || w >= TINY_W) {
-                                    atomicAdd(&tu[t], fixed64(w * W_SCALE));
+                                    atomicAdd(&tu[t], fixed64(w * W_SCALE_F32));
                                     atomicAdd(&tu[CT + t], fixed64(w * m0));
                                     atomicAdd(&tu[2 * CT + t], fixed64(w * m1));
                                     atomicAdd(&tu[3 * CT + t], fixed64(w * m2));
@@ -551,44 +583,49 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, con
                     scatter(std::true_type{});
                 else
                     scatter(std::false_type{});
-            } else {
-                if (!in_zone)
-                    activate_blocks(st, P.NB, sc.brick_base, brick_state, ovf, &ctl[CTL_OVF + parity], nbricks, err);
-                int xo[3], yo[3], zo[3];
-                axis_offsets(st.base[0], 1, 0, xo);
-                axis_offsets(st.base[1], P.NB, 2, yo);
-                axis_offsets(st.base[2], P.NB * P.NB, 4, zo);
-                float* accs = acc + 4 * (int64_t)sc.brick_base * BLOCK_NODES;
-                {  // the stencil's nodes lie in blocks (base >> 2) + 1 and ((base + 2) >> 2) + 1 per axis
-                    int* dirty = acc_dirty + sc.brick_base;
-                    const int bl[3] = {(st.base[0] >> 2) + 1, (st.base[1] >> 2) + 1, (st.base[2] >> 2) + 1};
-                    const int bh[3] = {((st.base[0] + 2) >> 2) + 1, ((st.base[1] + 2) >> 2) + 1,
-                                       ((st.base[2] + 2) >> 2) + 1};
+            }
+        } else if (tiled) {
+            tb = (st.base[0] - lo[0]) + R * (st.base[1] - lo[1]) + Q * (st.base[2] - lo[2]);
+            unsigned long long* tu = reinterpret_cast<unsigned long long*>(tq);
+            // weights times DENORM_SPLIT (in the z weights), momentum with the rest of the scale
+            double wx[3], wy[3], wz[3], ax[3], ay[3], az[3], mz[3];
+            const float ms = ldexpf(1.0f, FRAC_M - 74 - em);  // 2^(FRAC_M - em - 1074) / DENORM_SPLIT
+            const double k = (double)m_bound * (double)ms;
 #pragma unroll
-                    for (int k = 0; k < 8; ++k)
-                        dirty[((k & 4 ? bh[2] : bl[2]) * P.NB + (k & 2 ? bh[1] : bl[1])) * P.NB + (k & 1 ? bh[0] : bl[0])] = 1;
-                }
+            for (int o = 0; o < 3; ++o) {
+                wx[o] = (double)st.w[0][o];
+                wy[o] = (double)st.w[1][o];
+                wz[o] = (double)st.w[2][o] * DENORM_SPLIT;
+                mz[o] = (double)(q[o] * ms) + k;
+                ax[o] = (double)(Ad[3 * o] * ms);
+                ay[o] = (double)(Ad[3 * o + 1] * ms);
+                az[o] = (double)(Ad[3 * o + 2] * ms);
+            }
 #pragma unroll
-                for (int o2 = 0; o2 < 3; ++o2)
+            for (int o2 = 0; o2 < 3; ++o2) {
+                double my[3] = {mz[0], mz[1], mz[2]};
 #pragma unroll
-                    for (int o1 = 0; o1 < 3; ++o1) {
-                        const float wyz = st.w[1][o1] * st.w[2][o2];
-                        float m0 = q[0] + o1 * Ad[1] + o2 * Ad[2];
-                        float m1 = q[1] + o1 * Ad[4] + o2 * Ad[5];
-                        float m2 = q[2] + o1 * Ad[7] + o2 * Ad[8];
+                for (int o1 = 0; o1 < 3; ++o1) {
+                    const double wyz = wy[o1] * wz[o2];
+                    double m[3] = {my[0], my[1], my[2]};
+                    const int row = tb + R * o1 + Q * o2;
 #pragma unroll
-                        for (int o0 = 0; o0 < 3; ++o0) {
-                            const float w = wyz * st.w[0][o0];
-                            float* a = accs + 4 * (xo[o0] + yo[o1] + zo[o2]);
-                            unsafeAtomicAdd(a + 0, w * M.mp);
-                            unsafeAtomicAdd(a + 1, w * m0);
-                            unsafeAtomicAdd(a + 2, w * m1);
-                            unsafeAtomicAdd(a + 3, w * m2);
-                            m0 += Ad[0];
-                            m1 += Ad[3];
-                            m2 += Ad[6];
+                    for (int o0 = 0; o0 < 3; ++o0) {
+                        const double w = wyz * wx[o0];
+                        const int t = row + o0;
+                        // (one unit more, so that a node every weight of which rounds to nothing shows)
+                        atomicAdd(&tu[t], (unsigned long long)__double_as_longlong(fma(w, 0x1p-20, 0x1p-1074)));
+#pragma unroll
+                        for (int a = 0; a < 3; ++a) {
+                            atomicAdd(&tu[(a + 1) * CT + t], (unsigned long long)__double_as_longlong(w * m[a]));
+                            m[a] += ax[a];
                         }
                     }
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) my[a] += ay[a];
+                }
+#pragma unroll
+                for (int a = 0; a < 3; ++a) mz[a] += az[a];
             }
         }
 
@@ -598,18 +635,104 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, con
             float4* slot = stage + off;
             const int e01 = ext[0] * ext[1];
             const float r01 = 1.0f / (float)(e01 > 0 ? e01 : 1), r0 = 1.0f / (float)(ext[0] > 0 ? ext[0] : 1);
+            const double m_unit = ldexp(1.0, em - FRAC_M), mass_unit = 0x1p-54 * (double)M.mp;
+            const double k_unit = 0x1p-54 * (double)m_bound;
             for (int u = tid; u < nt; u += NT) {  // staged in the tight box layout
                 const int z = div_small(u, r01), u01 = u - z * e01;
                 const int y = div_small(u01, r0), xx = u01 - y * ext[0];
                 const int t = xx + R * y + Q * z;
-                const long long* ti = reinterpret_cast<const long long*>(tq);
-                const double mu = (double)m_unit;
-                slot[u] = make_float4((float)((double)ti[t] * (0x1p-51 * (double)M.mp)), (float)((double)ti[CT + t] * mu),
-                                      (float)((double)ti[2 * CT + t] * mu), (float)((double)ti[3 * CT + t] * mu));
+                const unsigned long long* tu = reinterpret_cast<const unsigned long long*>(tq);
+                const unsigned long long wsum = tu[t];
+                if constexpr (F32) {
+                    const double mu = (double)ldexpf(1.0f, em - FRAC_M_F32);
+                    slot[u] = make_float4((float)((double)(long long)wsum * (0x1p-51 * (double)M.mp)),
+                                          (float)((double)(long long)tu[CT + t] * mu),
+                                          (float)((double)(long long)tu[2 * CT + t] * mu),
+                                          (float)((double)(long long)tu[3 * CT + t] * mu));
+                } else if (wsum == 0ull || wsum >= WEAK_SUM) {
+                    const double wd = (double)wsum, kw = k_unit * wd;  // K times the weight sum
+                    slot[u] = make_float4((float)(wd * mass_unit), (float)((double)tu[CT + t] * m_unit - kw),
+                                          (float)((double)tu[2 * CT + t] * m_unit - kw),
+                                          (float)((double)tu[3 * CT + t] * m_unit - kw));
+                } else {
+                    weak[atomicAdd(&n_weak, 1)] = (unsigned short)(xx | (y << 5) | (z << 10));
+                }
 #pragma unroll
                 for (int ch4 = 0; ch4 < 4; ++ch4) tq[ch4 * CT + t] = 0.0;  // ready for the next chunk
             }
             __syncthreads();
+            const int nw = n_weak;  // uniform over the workgroup
+            if (nw > 0) {
+                for (int k0 = 0; k0 < nw; k0 += 64) {
+                    const int mine = k0 + lane < nw ? weak[k0 + lane] : 0;
+                    for (int k = 0; k < min(64, nw - k0); ++k) {
+                        const int e = __builtin_amdgcn_readlane(mine, k);
+                        const int wx = e & 31, wy = (e >> 5) & 31, wz = e >> 10;
+                        const unsigned o0 = lo[0] + wx - st.base[0], o1 = lo[1] + wy - st.base[1], o2 = lo[2] + wz - st.base[2];
+                        if (!tiled || o0 > 2u || o1 > 2u || o2 > 2u) continue;
+                        double* node = tq + wx + R * wy + Q * wz;
+                        const double w = (double)(pick3(st.w[1], o1) * pick3(st.w[2], o2)) * (double)pick3(st.w[0], o0);
+                        unsafeAtomicAdd(node, w);
+#pragma unroll
+                        for (int a = 0; a < 3; ++a)
+                            unsafeAtomicAdd(node + (a + 1) * CT,
+                                            w * (double)(q[a] + (float)o1 * Ad[3 * a + 1] + (float)o2 * Ad[3 * a + 2] +
+                                                         (float)o0 * Ad[3 * a]));
+                    }
+                }
+                __syncthreads();
+                if (tid == 0) n_weak = 0;  // (every thread has read it)
+                for (int k = tid; k < nw; k += NT) {
+                    const int e = weak[k], wx = e & 31, wy = (e >> 5) & 31, wz = e >> 10;
+                    double* node = tq + wx + R * wy + Q * wz;
+                    slot[wx + ext[0] * (wy + ext[1] * wz)] =
+                        make_float4((float)(node[0] * (double)M.mp), (float)node[CT], (float)node[2 * CT], (float)node[3 * CT]);
+#pragma unroll
+                    for (int ch4 = 0; ch4 < 4; ++ch4) node[ch4 * CT] = 0.0;
+                }
+                __syncthreads();
+            }
+        }
+
+        // ---- particles without a tile: straight to the global accumulators
+        if (have && ok && !tiled) {
+            if (!in_zone)
+                activate_blocks(st, P.NB, sc.brick_base, brick_state, ovf, &ctl[CTL_OVF + parity], nbricks, err);
+            int xo[3], yo[3], zo[3];
+            axis_offsets(st.base[0], 1, 0, xo);
+            axis_offsets(st.base[1], P.NB, 2, yo);
+            axis_offsets(st.base[2], P.NB * P.NB, 4, zo);
+            float* accs = acc + 4 * (int64_t)sc.brick_base * BLOCK_NODES;
+            {  // the stencil's nodes lie in blocks (base >> 2) + 1 and ((base + 2) >> 2) + 1 per axis
+                int* dirty = acc_dirty + sc.brick_base;
+                const int bl[3] = {(st.base[0] >> 2) + 1, (st.base[1] >> 2) + 1, (st.base[2] >> 2) + 1};
+                const int bh[3] = {((st.base[0] + 2) >> 2) + 1, ((st.base[1] + 2) >> 2) + 1,
+                                   ((st.base[2] + 2) >> 2) + 1};
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    dirty[((k & 4 ? bh[2] : bl[2]) * P.NB + (k & 2 ? bh[1] : bl[1])) * P.NB + (k & 1 ? bh[0] : bl[0])] = 1;
+            }
+#pragma unroll
+            for (int o2 = 0; o2 < 3; ++o2)
+#pragma unroll
+                for (int o1 = 0; o1 < 3; ++o1) {
+                    const float wyz = st.w[1][o1] * st.w[2][o2];
+                    float m0 = q[0] + o1 * Ad[1] + o2 * Ad[2];
+                    float m1 = q[1] + o1 * Ad[4] + o2 * Ad[5];
+                    float m2 = q[2] + o1 * Ad[7] + o2 * Ad[8];
+#pragma unroll
+                    for (int o0 = 0; o0 < 3; ++o0) {
+                        const float w = wyz * st.w[0][o0];
+                        float* a = accs + 4 * (xo[o0] + yo[o1] + zo[o2]);
+                        unsafeAtomicAdd(a + 0, w * M.mp);
+                        unsafeAtomicAdd(a + 1, w * m0);
+                        unsafeAtomicAdd(a + 2, w * m1);
+                        unsafeAtomicAdd(a + 3, w * m2);
+                        m0 += Ad[0];
+                        m1 += Ad[3];
+                        m2 += Ad[6];
+                    }
+                }
         }
     }
     if constexpr (FUSED) {
@@ -698,6 +821,11 @@ __global__ __launch_bounds__(NT) void k_p2g(MPM_P2G_PARAMS) {
     p2g_body<GLOBAL_ONLY, NT, SURM, false>(MPM_P2G_ARGS);
 }
 
+template <int NT>
+__global__ __launch_bounds__(NT) void k_p2g_f32(MPM_P2G_PARAMS) {
+    p2g_body<false, NT, 0, false, true>(MPM_P2G_ARGS);
+}
+
 // The fused form holds the gathered v and C beside the P2G state; four
 // waves per SIMD (at most 128 VGPRs) keep it as resident as the plain form.
 template <int NT>
@@ -729,7 +857,7 @@ int p2g_grid_size(int cus, int chunk) {
 
 void enqueue_p2g(hipStream_t st, const Launch& L, const Scenes& T, float* S, int64_t cap, const Chunk* chunks,
                  int* ctl, GridBuffers& G, int* brick_state, int pending, int parity, int global_atomics,
-                 int nbricks, int chunk, int act, int fused, int* host_flag, int fb_limit) {
+                 int nbricks, int chunk, int act, int fused, int* host_flag, int fb_limit, int f32) {
     const int nt = chunk_threads(chunk);
     const int surm = T.sur_any;  // 0, 1 (closed form) or 2 (network)
     auto launch = [&](auto kernel, int threads) {
@@ -745,6 +873,8 @@ void enqueue_p2g(hipStream_t st, const Launch& L, const Scenes& T, float* S, int
     } while (0)
     if (fused) {  // callers check: tile path, exact map
         if (nt == 128) launch(k_p2g_fused<128>, 128); else if (nt == 256) launch(k_p2g_fused<256>, 256); else launch(k_p2g_fused<512>, 512);
+    } else if (f32 && !global_atomics && surm == 0) {
+        if (nt == 128) launch(k_p2g_f32<128>, 128); else if (nt == 256) launch(k_p2g_f32<256>, 256); else launch(k_p2g_f32<512>, 512);
     } else if (global_atomics) {
         if (surm == 2) MPM_LAUNCH_P2G_NT(true, 2); else if (surm == 1) MPM_LAUNCH_P2G_NT(true, 1); else MPM_LAUNCH_P2G_NT(true, 0);
     } else {
