@@ -1374,8 +1374,7 @@ struct mpm_surrogate {
     float* v = nullptr;
     float* loss = nullptr;   // [loss_cap] per-step minibatch losses
     int loss_cap = 0;
-    int* idx = nullptr;      // minibatch rows
-    int idx_cap = 0;
+    void* work = nullptr;    // partial sums of the gradient or of the normalisation (sur_workspace_bytes)
     int step = 0;            // Adam steps taken
     unsigned long long* counter = nullptr;
 };
@@ -1414,6 +1413,7 @@ int mpm_surrogate_create(uint64_t stream, mpm_surrogate** out) {
               hipMalloc(&s->grad, sizeof(float) * SUR_PARAMS) == hipSuccess &&
               hipMalloc(&s->m, sizeof(float) * SUR_PARAMS) == hipSuccess &&
               hipMalloc(&s->v, sizeof(float) * SUR_PARAMS) == hipSuccess &&
+              hipMalloc(&s->work, sur_workspace_bytes()) == hipSuccess &&
               hipMalloc(&s->counter, sizeof(unsigned long long)) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
@@ -1442,7 +1442,7 @@ int mpm_surrogate_destroy(mpm_surrogate* s) {
     (void)hipFree(s->m);
     (void)hipFree(s->v);
     (void)hipFree(s->loss);
-    (void)hipFree(s->idx);
+    (void)hipFree(s->work);
     (void)hipFree(s->counter);
     delete s;
     return MPM_OK;
@@ -1474,14 +1474,17 @@ int mpm_surrogate_loss_grad(mpm_surrogate* s, int32_t precision, int64_t count, 
                             float* grad, float* loss) {
     if (!s || count < 1 || !X || !T || !grad || !loss || (precision != 0 && precision != 1))
         return sfail(s, MPM_EINVAL, "bad surrogate gradient arguments");
-    sur_grad(s->stream, precision, s->theta, s->norm, X, T, count, nullptr, grad, loss, true);
+    if (precision == MPM_SUR_BF16)
+        sur_grad16(s->stream, s->theta, s->norm, X, T, count, grad, loss, s->work);
+    else
+        sur_grad_fp32(s->stream, s->theta, s->norm, X, T, count, grad, loss);
     SHIP_OK(hipGetLastError());
     return MPM_OK;
 }
 
 int mpm_surrogate_fit_norm(mpm_surrogate* s, int64_t count, const float* X, const float* T) {
     if (!s || count < 1 || !X || !T) return sfail(s, MPM_EINVAL, "bad normalisation arguments");
-    sur_norm(s->stream, X, T, count, s->norm);
+    sur_norm(s->stream, X, T, count, s->norm, s->work);
     SHIP_OK(hipGetLastError());
     return MPM_OK;
 }
@@ -1490,15 +1493,13 @@ int mpm_surrogate_fit_norm(mpm_surrogate* s, int64_t count, const float* X, cons
 
 namespace {
 
-// `steps` Adam steps with the minibatch rows in idx[batch] and the per-step
-// losses in loss[steps] (device scratch of the caller's choosing), then the
-// losses to loss_host and a stream synchronization.
+// `steps` Adam steps with the per-step losses in loss[steps] (device scratch
+// of the caller's choosing), then the losses to loss_host and a stream
+// synchronization.
 int train_steps(mpm_surrogate* s, int64_t count, const float* X, const float* T, int32_t steps, int32_t batch,
-                float lr, uint64_t seed, float* loss_host, int* idx, float* loss) {
+                float lr, uint64_t seed, float* loss_host, float* loss) {
     for (int k = 0; k < steps; ++k) {
-        sur_indices(s->stream, seed, s->step, batch, count, idx);
-        sur_grad(s->stream, 1, s->theta, s->norm, X, T, batch, idx, s->grad, loss + k, true);
-        sur_adam(s->stream, s->theta, s->grad, s->m, s->v, s->step + 1, lr);
+        sur_train_step(s->stream, s->theta, s->norm, X, T, count, batch, seed, s->step, s->m, s->v, lr, loss + k, s->work);
         ++s->step;
     }
     SHIP_OK(hipGetLastError());
@@ -1516,13 +1517,12 @@ int check_train_args(mpm_surrogate* s, int64_t count, const float* X, const floa
     return MPM_OK;
 }
 
-// Scratch of mpm_surrogate_train_noalloc: the minibatch row indices
-// [MPM_SUR_NOALLOC_MAX_BATCH], then the per-step losses
+// Scratch of mpm_surrogate_train_noalloc: the per-step losses
 // [MPM_SUR_NOALLOC_MAX_STEPS] (FP32 bits).  Each device holds its own copy
 // for the life of the process.  In host code the name stands for no device
 // address: kernels get the address hipGetSymbolAddress returns for the
 // current device (scratch_on_device).
-__device__ __align__(256) int scratch[MPM_SUR_NOALLOC_MAX_BATCH + MPM_SUR_NOALLOC_MAX_STEPS];
+__device__ __align__(256) int scratch[MPM_SUR_NOALLOC_MAX_STEPS];
 
 constexpr int SCRATCH_MAX_DEVICES = 64;
 int* g_scratch_dev[SCRATCH_MAX_DEVICES];  // per device, filled on the entry point's first call there
@@ -1555,19 +1555,13 @@ extern "C" {
 int mpm_surrogate_train(mpm_surrogate* s, int64_t count, const float* X, const float* T, int32_t steps, int32_t batch,
                         float lr, uint64_t seed, float* loss_host) {
     if (int r = check_train_args(s, count, X, T, steps, batch, lr)) return r;
-    if (batch > s->idx_cap) {
-        (void)hipFree(s->idx);
-        s->idx = nullptr;
-        SHIP_OK(hipMalloc(&s->idx, sizeof(int) * batch));
-        s->idx_cap = batch;
-    }
     if (steps > s->loss_cap) {
         (void)hipFree(s->loss);
         s->loss = nullptr;
         SHIP_OK(hipMalloc(&s->loss, sizeof(float) * steps));
         s->loss_cap = steps;
     }
-    return train_steps(s, count, X, T, steps, batch, lr, seed, loss_host, s->idx, s->loss);
+    return train_steps(s, count, X, T, steps, batch, lr, seed, loss_host, s->loss);
 }
 
 int mpm_surrogate_train_noalloc(mpm_surrogate* s, int64_t count, const float* X, const float* T, int32_t steps,
@@ -1580,10 +1574,8 @@ int mpm_surrogate_train_noalloc(mpm_surrogate* s, int64_t count, const float* X,
     int* ptr = scratch_on_device(&e);
     if (!ptr)
         return sfail(s, MPM_EDEVICE, std::string("scratch address lookup failed: ") + hipGetErrorString(e));
-    // every index is written by the step that reads it and every loss slot is
-    // cleared by its step, so nothing left from an earlier call is read
-    return train_steps(s, count, X, T, steps, batch, lr, seed, loss_host, ptr,
-                       reinterpret_cast<float*>(ptr + MPM_SUR_NOALLOC_MAX_BATCH));
+    // every loss slot is written by its step, so nothing left from an earlier call is read
+    return train_steps(s, count, X, T, steps, batch, lr, seed, loss_host, reinterpret_cast<float*>(ptr));
 }
 
 int mpm_use_surrogate(mpm_ctx* c, int32_t scene, const mpm_surrogate* s, int32_t mode, float tol, float dt_ref) {

@@ -299,7 +299,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, con
     __shared__ typename std::conditional<SURM == 2, mlp::NetLds16, Empty>::type net;
     __shared__ __attribute__((aligned(16))) float sur_stage[SURM == 2 ? NT / 64 * mlp::FWD_STAGE : 1];
     if constexpr (SURM == 2) {
-        if (T.sur_theta) mlp::load_net16(net, T.sur_theta, T.sur_norm);
+        if (T.sur_theta) mlp::load_net16<NT>(net, T.sur_theta, T.sur_norm);
         __syncthreads();
     }
     int begin, end, stride;
@@ -765,7 +765,7 @@ __global__ __launch_bounds__(NT) void k_materialize_map(float* __restrict__ S, i
     __shared__ typename std::conditional<SURM == 2, mlp::NetLds16, Empty>::type net;
     __shared__ __attribute__((aligned(16))) float sur_stage[SURM == 2 ? NT / 64 * mlp::FWD_STAGE : 1];
     if constexpr (SURM == 2) {
-        if (T.sur_theta) mlp::load_net16(net, T.sur_theta, T.sur_norm);
+        if (T.sur_theta) mlp::load_net16<NT>(net, T.sur_theta, T.sur_norm);
         __syncthreads();
     }
     const int nchunk = ctl[CTL_NCHUNK];

@@ -26,13 +26,19 @@ constexpr int SUR_NORM = 2 * (SUR_IN + SUR_OUT);
 
 void sur_forward(hipStream_t st, int bf16, const float* th, const float* norm, const float* X, int64_t count,
                  float* Y);
-// Zeroes grad and loss first when `zero`; idx (may be NULL) selects the rows of X and T.
-void sur_grad(hipStream_t st, int bf16, const float* th, const float* norm, const float* X, const float* T,
-              int64_t count, const int* idx, float* grad, float* loss, bool zero);
-void sur_adam(hipStream_t st, float* th, float* grad, float* m, float* v, int step, float lr);
+// Loss and gradient over the rows of X and T: FP32 operands, or BF16 operands.  `work`:
+// sur_workspace_bytes() of device memory, owned by the caller, free again when the call's work has run.
+constexpr int SUR_MAX_PARTS = 256;  // workgroups of the BF16 gradient
+int64_t sur_workspace_bytes();
+void sur_grad_fp32(hipStream_t st, const float* th, const float* norm, const float* X, const float* T, int64_t count,
+                   float* grad, float* loss);
+void sur_grad16(hipStream_t st, const float* th, const float* norm, const float* X, const float* T, int64_t count,
+                float* grad, float* loss, void* work);
+// Adam step `step` (from 0) on a minibatch of `batch` rows drawn by (seed, step); the batch's loss into *loss.
+void sur_train_step(hipStream_t st, float* th, const float* norm, const float* X, const float* T, int64_t count,
+                    int batch, uint64_t seed, int step, float* m, float* v, float lr, float* loss, void* work);
 void sur_zero(hipStream_t st, float* p, int n);
-void sur_norm(hipStream_t st, const float* X, const float* T, int64_t count, float* norm);
-void sur_indices(hipStream_t st, uint64_t seed, int step, int batch, int64_t count, int* idx);
+void sur_norm(hipStream_t st, const float* X, const float* T, int64_t count, float* norm, void* work);
 struct Scenes;
 void sur_sample(hipStream_t st, const float* S, int64_t cap, int N, const Scenes& T, int scene, int pending, float E,
                 float dt_ref, int64_t max_rows, float* X, float* Y, unsigned long long* counter);
