@@ -222,12 +222,14 @@ Scenes tables(const mpm_ctx* c) {
     return T;
 }
 
+// Radix histogram tiles (2048 keys each at the least) and partial sums of the
+// rebuild's scans (2048 entries a tile; two sums a tile for the blocks; the
+// chunk scan takes 256 groups a tile).
+int64_t radix_tiles(int64_t cap) { return (cap + 2047) / 2048; }
 int scan_tiles_needed(int64_t cap, int nbricks) {
-    int64_t rs_tiles = (cap + 4095) / 4096;
-    int64_t m = cap;
-    if (nbricks > m) m = nbricks;
-    if (256 * rs_tiles > m) m = 256 * rs_tiles;
-    return (int)((m + 2047) / 2048) + 1;
+    const int64_t entries = std::max({cap, (int64_t)nbricks, 256 * radix_tiles(cap)});
+    const int64_t groups = std::min(cap, (int64_t)nbricks);
+    return (int)std::max({(entries + 2047) / 2048, 2 * ((cap + 2047) / 2048), (groups + 255) / 256}) + 1;
 }
 
 void free_particle_buffers(mpm_ctx* c) {
@@ -269,7 +271,7 @@ int grow(mpm_ctx* c, int64_t newcap) {
     int *group_start = nullptr, *sorted_ids = nullptr;
     float4* stage = nullptr;
     int4* box = nullptr;
-    const int64_t rs_tiles = (newcap + 4095) / 4096;
+    const int64_t rs_tiles = radix_tiles(newcap);
     // P2G staging: 16 nodes per particle of capacity (a block-sized chunk stages about one node per
     // particle) plus two full tiles per P2G workgroup, so small systems never run short.
     int64_t stage_nodes = 16 * newcap + 2 * 512 * (int64_t)c->L.p2g_grid;

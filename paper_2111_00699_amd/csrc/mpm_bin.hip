@@ -23,8 +23,15 @@ namespace mpm {
 
 namespace {
 
-constexpr int RS_ITEMS = 16;
-constexpr int RS_TILE = WG * RS_ITEMS;  // 4096 keys per radix tile
+// Radix tiles: 4096 keys, or 2048 up to RS_DIRECT_TILES of those.  Few tiles
+// leave most CUs idle, and the smaller ones halve the rounds of a tile; up to
+// that count a scatter workgroup also adds up the tiles' histograms itself
+// (one coalesced row of 256 counts per tile, all loads in flight) instead of
+// reading them scanned, which saves the scan's two launches per pass.  With
+// 143K particles a pass takes 14 us that way and 29 us with 4096-key tiles and
+// the scan; with 1M the rows would be 512, read by 512 workgroups.
+constexpr int RS_LARGE = 16, RS_SMALL = 8;  // keys per thread
+constexpr int RS_DIRECT_TILES = 128;
 constexpr int SCAN_ITEMS = 8;
 constexpr int SCAN_TILE = WG * SCAN_ITEMS;  // 2048 entries per scan tile
 
@@ -64,71 +71,113 @@ __device__ __forceinline__ int block_excl_scan(int v, int* total) {
 // n, x*n is exact in FP32 and x*n - 1/2 is exact wherever it matters, so the
 // code is bit-identical to one computed in FP64 from the same FP32 x.  The
 // scene's rank goes above the Morton bits.
+// A workgroup takes one radix tile and also counts the digits of the first pass.
+template <int ITEMS, bool DIRECT>
 __global__ __launch_bounds__(WG) void k_keys(const float* __restrict__ S, int64_t cap, int N, Scenes T,
                                              uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
-                                             int* __restrict__ ctl) {
-    const int j = blockIdx.x * WG + threadIdx.x;
-    if (j >= N) return;
-    const Scene& sc = T.scene[fsid_scene(S[sidx(FSID, j, cap)])];
-    const float fn = sc.P.fn;
-    const int n = sc.P.n;
-    uint32_t code = (uint32_t)sc.rank << T.shift;
+                                             int* __restrict__ ctl, int tiles, int* __restrict__ hist) {
+    __shared__ int h[256];
+    h[threadIdx.x] = 0;
+    __syncthreads();
+    const int first = blockIdx.x * (WG * ITEMS) + threadIdx.x;
+    float id[ITEMS], x[ITEMS][3];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const int j = min(first + r * WG, N - 1);
+        id[r] = S[sidx(FSID, j, cap)];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) x[r][a] = S[sidx(FX + a, j, cap)];
+    }
     unsigned err = 0;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const float x = S[sidx(FX + a, j, cap)];
-        const float b = floorf(x * fn - 0.5f);
-        int c;
-        if (!(b == b)) {
-            err |= MPM_ERR_NONFINITE;
-            c = 0;
-        } else {
-            if (!(b >= 0.0f && b <= (float)(n - 2))) err |= MPM_ERR_DOMAIN;
-            c = (int)fminf(fmaxf(b + 1.0f, 0.0f), (float)(n - 1));
+    for (int r = 0; r < ITEMS; ++r) {
+        const int j = first + r * WG;
+        if (j >= N) break;
+        const Scene& sc = T.scene[T.S == 1 ? 0 : fsid_scene(id[r])];
+        const float fn = sc.P.fn;
+        const int n = sc.P.n;
+        uint32_t code = (uint32_t)sc.rank << T.shift;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float b = floorf(x[r][a] * fn - 0.5f);
+            int c;
+            if (!(b == b)) {
+                err |= MPM_ERR_NONFINITE;
+                c = 0;
+            } else {
+                if (!(b >= 0.0f && b <= (float)(n - 2))) err |= MPM_ERR_DOMAIN;
+                c = (int)fminf(fmaxf(b + 1.0f, 0.0f), (float)(n - 1));
+            }
+            code |= spread3((uint32_t)c) << a;
         }
-        code |= spread3((uint32_t)c) << a;
+        keys[j] = code;
+        vals[j] = (uint32_t)j;
+        atomicAdd(&h[code & 255u], 1);
     }
-    keys[j] = code;
-    vals[j] = (uint32_t)j;
     if (err) atomicOr(&ctl[CTL_ERROR], (int)err);
+    __syncthreads();
+    hist[DIRECT ? blockIdx.x * 256 + threadIdx.x : threadIdx.x * tiles + blockIdx.x] = h[threadIdx.x];
 }
 
 // --------------------------------------------------------------- radix sort
+// Digit counts of each tile: DIRECT [tile][digit], else [digit][tile] (for the scan).
+template <int ITEMS, bool DIRECT>
 __global__ __launch_bounds__(WG) void k_rs_hist(const uint32_t* __restrict__ keys, int N, int shift, int tiles,
                                                 int* __restrict__ hist) {
     __shared__ int h[256];
     h[threadIdx.x] = 0;
     __syncthreads();
-    const int base = blockIdx.x * RS_TILE;
+    const int base = blockIdx.x * (WG * ITEMS);
 #pragma unroll
-    for (int r = 0; r < RS_ITEMS; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         const int i = base + r * WG + threadIdx.x;
         if (i < N) atomicAdd(&h[(keys[i] >> shift) & 255u], 1);
     }
     __syncthreads();
-    hist[threadIdx.x * tiles + blockIdx.x] = h[threadIdx.x];
+    hist[DIRECT ? blockIdx.x * 256 + threadIdx.x : threadIdx.x * tiles + blockIdx.x] = h[threadIdx.x];
 }
 
 // Stable scatter: keys of the tile are taken in order, 256 at a time; inside
 // a wave the rank among lanes with the same digit comes from eight ballots,
-// across the four waves from per-wave digit counts in LDS.
+// across the four waves from per-wave digit counts in LDS.  The tile's keys
+// are loaded before the first round (a load per round made the kernel wait
+// for memory 16 times).  offs: the scanned histogram, or (DIRECT) the plain one.
+template <int ITEMS, bool DIRECT>
 __global__ __launch_bounds__(WG) void k_rs_scatter(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
                                                    uint32_t* __restrict__ kout, uint32_t* __restrict__ vout, int N,
                                                    int shift, int tiles, const int* __restrict__ offs) {
     __shared__ int base[256];
     __shared__ int wcnt[WG / 64][256];
     const int tid = threadIdx.x, w = tid >> 6, lane = lane_id();
-    base[tid] = offs[tid * tiles + blockIdx.x];
+    const int first = blockIdx.x * (WG * ITEMS) + tid;
+    uint32_t key[ITEMS], val[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const int i = min(first + r * WG, N - 1);
+        key[r] = kin[i];
+        val[r] = vin[i];
+    }
+    if constexpr (DIRECT) {
+        int all = 0, before = 0;
+#pragma unroll 16
+        for (int t = 0; t < tiles; ++t) {
+            const int v = offs[t * 256 + tid];
+            all += v;
+            before += t < (int)blockIdx.x ? v : 0;
+        }
+        int total;
+        base[tid] = block_excl_scan(all, &total) + before;
+    } else {
+        base[tid] = offs[tid * tiles + blockIdx.x];
+    }
 #pragma unroll
     for (int i = 0; i < WG / 64; ++i) wcnt[i][tid] = 0;
     __syncthreads();
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    for (int r = 0; r < RS_ITEMS; ++r) {
-        const int i = blockIdx.x * RS_TILE + r * WG + tid;
-        const bool valid = i < N;
-        const uint32_t key = valid ? kin[i] : 0u;
-        const uint32_t val = valid ? vin[i] : 0u;
-        const uint32_t d = (key >> shift) & 255u;
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const bool valid = first + r * WG < N;
+        const uint32_t d = (key[r] >> shift) & 255u;
         uint64_t peers = __ballot(valid);
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
@@ -143,8 +192,8 @@ __global__ __launch_bounds__(WG) void k_rs_scatter(const uint32_t* __restrict__ 
             int off = base[d] + rank;
 #pragma unroll
             for (int k = 0; k < WG / 64; ++k) off += (k < w) ? wcnt[k][d] : 0;
-            kout[off] = key;
-            vout[off] = val;
+            kout[off] = key[r];
+            vout[off] = val[r];
         }
         __syncthreads();
         int add = 0;
@@ -159,97 +208,144 @@ __global__ __launch_bounds__(WG) void k_rs_scatter(const uint32_t* __restrict__ 
 }
 
 // --------------------------------------------------------- generic scan
-// Three launches: per-tile totals, a one-workgroup scan of the totals, and a
-// per-tile exclusive scan that hands each element its output offset.
-template <class Op>
+// Two launches: per-tile totals, and a per-tile exclusive scan that hands each
+// element its output offset; a workgroup of the second adds up the totals of
+// the tiles before its own (a few thousand at most, read coalesced), which a
+// launch of its own between the two did before.  op.limit(n): entries from
+// there on count nothing (workgroups past it leave at once).
+template <int ITEMS, class Op>
 __global__ __launch_bounds__(WG) void k_scan_count(Op op, int n, int* __restrict__ tile_sums) {
-    const int first = blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
+    const int first = blockIdx.x * (WG * ITEMS) + threadIdx.x * ITEMS;
+    n = op.limit(n);
+    if ((int)blockIdx.x * (WG * ITEMS) >= n) return;
     int s = 0;
 #pragma unroll
-    for (int i = 0; i < SCAN_ITEMS; ++i)
+    for (int i = 0; i < ITEMS; ++i)
         if (first + i < n) s += op.count(first + i);
     int tot;
     block_excl_scan(s, &tot);
     if (threadIdx.x == 0) tile_sums[blockIdx.x] = tot;
 }
 
-__global__ __launch_bounds__(WG) void k_scan_top(int* __restrict__ a, int n, int* __restrict__ total) {
-    int carry = 0;
-    for (int base = 0; base < n; base += WG) {
-        const int i = base + threadIdx.x;
-        const int v = i < n ? a[i] : 0;
-        int tot;
-        const int ex = block_excl_scan(v, &tot);
-        if (i < n) a[i] = carry + ex;
-        carry += tot;
-    }
-    if (threadIdx.x == 0) *total = carry;
+// Sum of a[0 .. n) over the workgroup's threads.
+__device__ __forceinline__ int block_sum(const int* __restrict__ a, int n) {
+    int s = 0;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < n; i += WG) s += a[i];
+    int tot;
+    block_excl_scan(s, &tot);
+    return tot;
 }
 
-template <class Op>
-__global__ __launch_bounds__(WG) void k_scan_emit(Op op, int n, const int* __restrict__ tile_offs) {
-    const int first = blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
-    int c[SCAN_ITEMS];
+template <int ITEMS, class Op>
+__global__ __launch_bounds__(WG) void k_scan_emit(Op op, int n, const int* __restrict__ tile_sums,
+                                                  int* __restrict__ total) {
+    const int first = blockIdx.x * (WG * ITEMS) + threadIdx.x * ITEMS;
+    n = op.limit(n);
+    const int last = n > 0 ? (n - 1) / (WG * ITEMS) : 0;  // the workgroup that ends the scan
+    if ((int)blockIdx.x > last) return;
+    int c[ITEMS];
     int s = 0;
 #pragma unroll
-    for (int i = 0; i < SCAN_ITEMS; ++i) {
+    for (int i = 0; i < ITEMS; ++i) {
         c[i] = (first + i < n) ? op.count(first + i) : 0;
         s += c[i];
     }
+    const int before = block_sum(tile_sums, blockIdx.x);
     int tot;
-    int off = tile_offs[blockIdx.x] + block_excl_scan(s, &tot);
+    int off = before + block_excl_scan(s, &tot);
+    if ((int)blockIdx.x == last && threadIdx.x == 0) *total = before + tot;
 #pragma unroll
-    for (int i = 0; i < SCAN_ITEMS; ++i) {
+    for (int i = 0; i < ITEMS; ++i) {
         if (c[i] > 0) op.emit(first + i, off, c[i]);
         off += c[i];
     }
 }
 
-template <class Op>
+template <int ITEMS = SCAN_ITEMS, class Op>
 void device_scan(hipStream_t st, const Op& op, int n, int* tile_sums, int* total) {
-    const int tiles = cdiv(n > 0 ? n : 1, SCAN_TILE);
-    hipLaunchKernelGGL(k_scan_count<Op>, dim3(tiles), dim3(WG), 0, st, op, n, tile_sums);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(WG), 0, st, tile_sums, tiles, total);
-    hipLaunchKernelGGL(k_scan_emit<Op>, dim3(tiles), dim3(WG), 0, st, op, n, tile_sums);
+    const int tiles = cdiv(n > 0 ? n : 1, WG * ITEMS);
+    hipLaunchKernelGGL((k_scan_count<ITEMS, Op>), dim3(tiles), dim3(WG), 0, st, op, n, tile_sums);
+    hipLaunchKernelGGL((k_scan_emit<ITEMS, Op>), dim3(tiles), dim3(WG), 0, st, op, n, tile_sums, total);
 }
 
 struct OpHistScan {  // exclusive scan of the radix histogram in place
     int* h;
+    __device__ int limit(int n) const { return n; }
     __device__ int count(int i) const { return h[i]; }
     __device__ void emit(int i, int off, int) const { h[i] = off; }
 };
 
-// Geometric blocks: positions where the block code (code >> 6) changes.
-struct OpGBlocks {
-    const uint32_t* keys;
-    int N;
-    int* gstart;
-    uint32_t* gcode;
-    __device__ int count(int j) const { return (j == 0 || (keys[j] >> 6) != (keys[j - 1] >> 6)) ? 1 : 0; }
-    __device__ void emit(int j, int off, int) const {
-        gstart[off] = j;
-        gcode[off] = keys[j] >> 6;
-    }
-};
+// Geometric blocks: positions where the block code (code >> 6) changes, and
+// merge groups: runs of geometric blocks of one 2x2x1 slab of blocks (equal
+// code >> 8; the rank bits make groups never cross scenes; without `pack`
+// every block is a group of its own).  Both in one scan over the sorted codes.
+__device__ __forceinline__ void block_heads(const uint32_t* keys, int j, int N, int pack, int& gb, int& gr) {
+    gb = gr = 0;
+    if (j >= N) return;
+    const uint32_t k = keys[j], p = j > 0 ? keys[j - 1] : ~k;
+    gb = (k >> 6) != (p >> 6) || j == 0 ? 1 : 0;
+    gr = pack ? ((k >> 8) != (p >> 8) || j == 0 ? 1 : 0) : gb;
+}
 
-// Merge groups: runs of geometric blocks of one 2x2x1 slab of blocks (equal
-// code >> 2; the rank bits make groups never cross scenes).
-struct OpGroups {
-    const uint32_t* gcode;
-    int* group_start;
-    const int* ctl;
-    int pack;  // 0: every block is a group of its own (one block per chunk)
-    __device__ int count(int g) const {
-        if (g >= ctl[CTL_NGB]) return 0;
-        return (g == 0 || !pack || (gcode[g] >> 2) != (gcode[g - 1] >> 2)) ? 1 : 0;
+__global__ __launch_bounds__(WG) void k_blocks_count(const uint32_t* __restrict__ keys, int N, int pack, int tiles,
+                                                     int* __restrict__ sums) {
+    const int first = blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
+    int s0 = 0, s1 = 0;
+#pragma unroll
+    for (int i = 0; i < SCAN_ITEMS; ++i) {
+        int gb, gr;
+        block_heads(keys, first + i, N, pack, gb, gr);
+        s0 += gb;
+        s1 += gr;
     }
-    __device__ void emit(int g, int off, int) const { group_start[off] = g; }
-};
+    int t0, t1;
+    block_excl_scan(s0, &t0);
+    block_excl_scan(s1, &t1);
+    if (threadIdx.x == 0) {
+        sums[blockIdx.x] = t0;
+        sums[tiles + blockIdx.x] = t1;
+    }
+}
+
+__global__ __launch_bounds__(WG) void k_blocks_emit(const uint32_t* __restrict__ keys, int N, int pack, int tiles,
+                                                    const int* __restrict__ sums, int* __restrict__ gstart,
+                                                    uint32_t* __restrict__ gcode, int* __restrict__ group_start,
+                                                    int* __restrict__ ctl) {
+    const int first = blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
+    int gb[SCAN_ITEMS], gr[SCAN_ITEMS], s0 = 0, s1 = 0;
+#pragma unroll
+    for (int i = 0; i < SCAN_ITEMS; ++i) {
+        block_heads(keys, first + i, N, pack, gb[i], gr[i]);
+        s0 += gb[i];
+        s1 += gr[i];
+    }
+    const int b0 = block_sum(sums, blockIdx.x), b1 = block_sum(sums + tiles, blockIdx.x);
+    int t0, t1;
+    int o0 = b0 + block_excl_scan(s0, &t0), o1 = b1 + block_excl_scan(s1, &t1);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        ctl[CTL_NGB] = b0 + t0;
+        ctl[CTL_NGROUP] = b1 + t1;
+    }
+#pragma unroll
+    for (int i = 0; i < SCAN_ITEMS; ++i) {
+        if (gb[i]) {
+            gstart[o0] = first + i;
+            gcode[o0] = keys[first + i] >> 6;
+        }
+        if (gr[i]) group_start[o1] = o0;
+        o0 += gb[i];
+        o1 += gr[i];
+    }
+}
 
 // Work chunks, per merge group: consecutive blocks are packed into one chunk
 // while the total stays within `chunk` particles; a block larger than that
 // is cut into runs of `chunk`.  (Sparse regions then still fill the
 // workgroups; a chunk's tile box stays within a 2x2x1 slab of blocks.)
+// One group per thread: the walk over a group's blocks is a chain of
+// dependent loads, which a thread with eight groups walked eight times (46 us
+// at 143K particles; 4 us so).
 struct OpChunks {
     const int* gstart;
     const uint32_t* gcode;
@@ -258,59 +354,64 @@ struct OpChunks {
     int N, chunk;
     Chunk* out;
     Scenes T;
-    __device__ int len(int g) const {
-        const int ng = ctl[CTL_NGB];
-        const int end = (g + 1 < ng) ? gstart[g + 1] : N;
-        return end - gstart[g];
-    }
-    __device__ int group_end(int s) const { return s + 1 < ctl[CTL_NGROUP] ? group_start[s + 1] : ctl[CTL_NGB]; }
-    // walk the group's blocks, calling put(start, count, first block) for each chunk
+    // walk the group's blocks, calling put(start, count) for each chunk
     template <class Put>
     __device__ int walk(int s, Put put) const {
-        int k = 0, run0 = -1, runn = 0, runb = 0;
-        for (int g = group_start[s]; g < group_end(s); ++g) {
-            const int l = len(g);
+        const int ngb = ctl[CTL_NGB], g0 = group_start[s];
+        const int g1 = s + 1 < ctl[CTL_NGROUP] ? group_start[s + 1] : ngb;
+        int st[5];  // a group has at most four blocks: their starts and the end
+#pragma unroll
+        for (int i = 0; i < 5; ++i) st[i] = g0 + i < ngb ? gstart[g0 + i] : N;
+        int k = 0, run0 = 0, runn = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (g0 + i >= g1) break;
+            const int l = st[i + 1] - st[i];
             if (l > chunk) {
-                if (runn) put(k++, run0, runn, runb);
+                if (runn) put(k++, run0, runn);
                 runn = 0;
-                for (int i = 0; i < l; i += chunk) put(k++, gstart[g] + i, min(chunk, l - i), g);
+                for (int j = 0; j < l; j += chunk) put(k++, st[i] + j, min(chunk, l - j));
             } else {
                 if (runn && runn + l > chunk) {
-                    put(k++, run0, runn, runb);
+                    put(k++, run0, runn);
                     runn = 0;
                 }
-                if (!runn) {
-                    run0 = gstart[g];
-                    runb = g;
-                }
+                if (!runn) run0 = st[i];
                 runn += l;
             }
         }
-        if (runn) put(k++, run0, runn, runb);
+        if (runn) put(k++, run0, runn);
         return k;
     }
+    __device__ int limit(int n) const { return min(n, ctl[CTL_NGROUP]); }
     __device__ int count(int s) const {
-        if (s >= ctl[CTL_NGROUP]) return 0;
-        return walk(s, [](int, int, int, int) {});
+        return walk(s, [](int, int, int) {});
     }
     __device__ void emit(int s, int off, int) const {
-        const int bshift = T.shift - 6;
-        walk(s, [&](int k, int start, int n, int g) {
+        const int scene = T.rank_scene[gcode[group_start[s]] >> (T.shift - 6)];  // a group is of one scene
+        walk(s, [&](int k, int start, int n) {
             Chunk c;
             c.start = start;
             c.count = n;
             c.tile = 1;
-            c.scene = T.rank_scene[gcode[g] >> bshift];
+            c.scene = scene;
             out[off + k] = c;
         });
     }
 };
 
+// Physical blocks in padded linear order; a block's state then names its
+// position in the active list (3 + i), under which the rebuild lists the
+// chunks whose tiles can reach it.
 struct OpActive {
-    const int* state;
+    int* state;
     int* active;
+    __device__ int limit(int n) const { return n; }
     __device__ int count(int b) const { return state[b] != 0 ? 1 : 0; }
-    __device__ void emit(int b, int off, int) const { active[off] = b; }
+    __device__ void emit(int b, int off, int) const {
+        active[off] = b;
+        state[b] = 3 + off;
+    }
 };
 
 // ------------------------------------------------------------ data movement
@@ -362,6 +463,16 @@ __global__ __launch_bounds__(WG) void k_permute_chunks(const float* __restrict__
     for (int c = blockIdx.x; c < nch; c += gridDim.x) {
         const Chunk ch = chunks[c];
         const bool deal = spread && ch.count <= PERMUTE_MAX;  // workgroup-uniform
+        // this thread's particle (the first pass) is loaded while the chunk is ranked
+        float q[NF];
+        int id = 0;
+        auto load = [&](int t) {
+            const int k = (int)src[ch.start + t];  // its position before the sort
+#pragma unroll
+            for (int f = 0; f < NF; ++f) q[f] = Sin[sidx(f, k, cap)];
+            id = idin[k];
+        };
+        if ((int)threadIdx.x < ch.count) load(threadIdx.x);
         if (deal) {
             // a counting sort of the ranking keys: histogram, then its exclusive prefix sums
             for (int t = threadIdx.x; t < NRK; t += WG) below[t] = 0;
@@ -393,6 +504,7 @@ __global__ __launch_bounds__(WG) void k_permute_chunks(const float* __restrict__
             __syncthreads();
         }
         for (int t = threadIdx.x; t < ch.count; t += WG) {
+            if (t >= WG) load(t);
             const int j = ch.start + t;  // sorted position
             const uint32_t key = keys[j];
             int slot = t;
@@ -406,16 +518,14 @@ __global__ __launch_bounds__(WG) void k_permute_chunks(const float* __restrict__
                 while (first > 0 && rk[first - 1] == mine) --first;
                 slot = dealt_slot(ch.count, below[mine] + (t - first));
             }
-            const int k = (int)src[j];  // its position before the sort
             const int dst = ch.start + slot;
 #pragma unroll
-            for (int f = 0; f < FSID; ++f) Sout[sidx(f, dst, cap)] = Sin[sidx(f, k, cap)];
+            for (int f = 0; f < FSID; ++f) Sout[sidx(f, dst, cap)] = q[f];
             const uint32_t bcode = (key & mmask) >> 6;
-            const int scene = fsid_scene(Sin[sidx(FSID, k, cap)]);
+            const int scene = fsid_scene(q[FSID]);
             Sout[sidx(FSID, dst, cap)] = __int_as_float(scene | (int)(compact3(bcode) << 8) |
                                                     (int)(compact3(bcode >> 1) << 16) |
                                                     (int)(compact3(bcode >> 2) << 24));
-            const int id = idin[k];
             idout[dst] = id;
             sorted_ids[j] = id;
         }
@@ -429,9 +539,9 @@ __global__ __launch_bounds__(WG) void k_copy_codes(uint32_t* __restrict__ dst, c
     if (i < n) dst[i] = src[i] & mask;
 }
 
-__global__ __launch_bounds__(WG) void k_fill(int* __restrict__ p, int v, int n) {
+__global__ __launch_bounds__(WG) void k_clear2(int* __restrict__ p, int* __restrict__ q, int n) {
     const int i = blockIdx.x * WG + threadIdx.x;
-    if (i < n) p[i] = v;
+    if (i < n) p[i] = q[i] = 0;
 }
 
 // Mark the 3x3x3 neighbourhood of every geometric block as physical, in
@@ -453,43 +563,38 @@ __global__ __launch_bounds__(WG) void k_dilate(const uint32_t* __restrict__ gcod
     }
 }
 
-// After compaction a physical block's state names its position in the active
-// list (3 + i), under which the rebuild lists the chunks whose tiles can reach
-// it.
-__global__ __launch_bounds__(WG) void k_mark_active(const int* __restrict__ active, const int* __restrict__ ctl,
-                                                    int* __restrict__ state) {
-    const int n = ctl[CTL_NACTIVE];
-    for (int i = blockIdx.x * WG + threadIdx.x; i < n; i += gridDim.x * WG) state[active[i]] = 3 + i;
-}
-
 // Per-rank ends of the sorted particles, geometric blocks, chunks and
-// physical blocks (binary searches over the rank-major lists).
+// physical blocks (binary searches over the rank-major lists, one per thread;
+// the last rank ends where its list does).  The rebuild also starts the
+// overflow lists and fallback counts afresh.
 __global__ __launch_bounds__(WG) void k_rank_ends(const uint32_t* __restrict__ keys, int N,
                                                   const uint32_t* __restrict__ gcode, const Chunk* __restrict__ chunks,
-                                                  const int* __restrict__ active, const int* __restrict__ ctl,
-                                                  Scenes T) {
-    for (int r = threadIdx.x; r < T.S; r += WG) {
-        auto upper = [&](int n, auto rank_at) {  // first index whose rank exceeds r
-            int lo = 0, hi = n;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (rank_at(mid) <= r)
-                    lo = mid + 1;
-                else
-                    hi = mid;
-            }
-            return lo;
-        };
-        T.rank_end[RE_PART * T.S + r] = upper(N, [&](int i) { return (int)(keys[i] >> T.shift); });
-        T.rank_end[RE_GBLOCK * T.S + r] =
-            upper(ctl[CTL_NGB], [&](int i) { return (int)(gcode[i] >> (T.shift - 6)); });
-        T.rank_end[RE_CHUNK * T.S + r] = upper(ctl[CTL_NCHUNK], [&](int i) { return T.scene[chunks[i].scene].rank; });
-        T.rank_end[RE_ACTIVE * T.S + r] =
-            upper(ctl[CTL_NACTIVE], [&](int i) { return active[i] >= T.rank_brick[r + 1] ? r + 1 : r; });
+                                                  const int* __restrict__ active, int* __restrict__ ctl, Scenes T) {
+    if (threadIdx.x == 0) {
+        ctl[CTL_REBUILD] = 0;
+        ctl[CTL_OVF] = ctl[CTL_OVF + 1] = 0;
+        ctl[CTL_FB] = ctl[CTL_FB + 1] = 0;
+    }
+    for (int t = threadIdx.x; t < 4 * T.S; t += WG) {
+        const int kind = t / T.S, r = t - kind * T.S;
+        const int n = kind == RE_PART ? N : ctl[kind == RE_GBLOCK ? CTL_NGB : kind == RE_CHUNK ? CTL_NCHUNK : CTL_NACTIVE];
+        int lo = 0, hi = n;
+        if (r == T.S - 1) lo = n;
+        while (lo < hi) {  // first index whose rank exceeds r
+            const int mid = (lo + hi) >> 1;
+            const int rank = kind == RE_PART     ? (int)(keys[mid] >> T.shift)
+                             : kind == RE_GBLOCK ? (int)(gcode[mid] >> (T.shift - 6))
+                             : kind == RE_CHUNK  ? T.scene[chunks[mid].scene].rank
+                                                 : (active[mid] >= T.rank_brick[r + 1] ? r + 1 : r);
+            if (rank <= r)
+                lo = mid + 1;
+            else
+                hi = mid;
+        }
+        T.rank_end[t] = lo;
     }
 }
 
-// The rebuild also starts the overflow lists and fallback counts afresh.
 // Tile registrations, one wave per chunk: the chunk's particle blocks (the
 // blocks of its sorted range, at most the four of one 2x2x1 slab) reach
 // padded blocks B .. B+2 per axis with in-zone stencils; the chunk is listed
@@ -566,12 +671,6 @@ __global__ __launch_bounds__(WG) void k_sort_registrations(const int* __restrict
     }
 }
 
-__global__ void k_finish_rebuild(int* ctl) {
-    ctl[CTL_REBUILD] = 0;
-    ctl[CTL_OVF] = ctl[CTL_OVF + 1] = 0;
-    ctl[CTL_FB] = ctl[CTL_FB + 1] = 0;
-}
-
 }  // namespace
 
 // The overflow-block and tile-fallback counts of both substep parities
@@ -595,40 +694,58 @@ void enqueue_rebuild(hipStream_t st, const Scenes& T, float* S_cur, float* S_alt
                      int64_t cap, int N, int chunk, int spread, int pack, BinBuffers& B, int* ctl, int nbricks,
                      int key_bits,
                      int* reg_n, int* reg) {
-    const int nb = cdiv(N > 0 ? N : 1, WG);
-    // 1. particle codes
-    hipLaunchKernelGGL(k_keys, dim3(nb), dim3(WG), 0, st, S_cur, cap, N, T, B.keys[0], B.vals[0], ctl);
-    // 2. stable radix sort of (code, position)
-    const int passes = (key_bits + 7) / 8;
-    const int tiles = cdiv(N > 0 ? N : 1, RS_TILE);
+    const int n1 = N > 0 ? N : 1;
+    const bool direct = cdiv(n1, WG * RS_SMALL) <= RS_DIRECT_TILES;
+    const int tiles = cdiv(n1, WG * (direct ? RS_SMALL : RS_LARGE));
+    // 1. particle codes, 2. stable radix sort of (code, position)
+    if (N > 0) {
+        if (direct)
+            hipLaunchKernelGGL((k_keys<RS_SMALL, true>), dim3(tiles), dim3(WG), 0, st, S_cur, cap, N, T, B.keys[0],
+                               B.vals[0], ctl, tiles, B.hist);
+        else
+            hipLaunchKernelGGL((k_keys<RS_LARGE, false>), dim3(tiles), dim3(WG), 0, st, S_cur, cap, N, T, B.keys[0],
+                               B.vals[0], ctl, tiles, B.hist);
+    }
+    const int passes = N > 0 ? (key_bits + 7) / 8 : 0;
     int cur = 0;
     for (int p = 0; p < passes; ++p) {
-        hipLaunchKernelGGL(k_rs_hist, dim3(tiles), dim3(WG), 0, st, B.keys[cur], N, 8 * p, tiles, B.hist);
-        device_scan(st, OpHistScan{B.hist}, 256 * tiles, B.scan_tiles, ctl + CTL_SCAN);
-        hipLaunchKernelGGL(k_rs_scatter, dim3(tiles), dim3(WG), 0, st, B.keys[cur], B.vals[cur], B.keys[cur ^ 1],
-                           B.vals[cur ^ 1], N, 8 * p, tiles, B.hist);
+        if (direct) {
+            if (p > 0)
+                hipLaunchKernelGGL((k_rs_hist<RS_SMALL, true>), dim3(tiles), dim3(WG), 0, st, B.keys[cur], N, 8 * p, tiles,
+                                   B.hist);
+            hipLaunchKernelGGL((k_rs_scatter<RS_SMALL, true>), dim3(tiles), dim3(WG), 0, st, B.keys[cur], B.vals[cur],
+                               B.keys[cur ^ 1], B.vals[cur ^ 1], N, 8 * p, tiles, B.hist);
+        } else {
+            if (p > 0)
+                hipLaunchKernelGGL((k_rs_hist<RS_LARGE, false>), dim3(tiles), dim3(WG), 0, st, B.keys[cur], N, 8 * p,
+                                   tiles, B.hist);
+            device_scan(st, OpHistScan{B.hist}, 256 * tiles, B.scan_tiles, ctl + CTL_SCAN);
+            hipLaunchKernelGGL((k_rs_scatter<RS_LARGE, false>), dim3(tiles), dim3(WG), 0, st, B.keys[cur], B.vals[cur],
+                               B.keys[cur ^ 1], B.vals[cur ^ 1], N, 8 * p, tiles, B.hist);
+        }
         cur ^= 1;
     }
     B.sorted = cur;  // slot holding the sorted codes and their source positions
-    // 3. geometric blocks and work chunks
-    device_scan(st, OpGBlocks{B.keys[cur], N, B.gstart, B.gcode}, N, B.scan_tiles, ctl + CTL_NGB);
-    device_scan(st, OpGroups{B.gcode, B.group_start, ctl, pack}, N, B.scan_tiles, ctl + CTL_NGROUP);
-    device_scan(st, OpChunks{B.gstart, B.gcode, B.group_start, ctl, N, chunk, B.chunks, T}, N, B.scan_tiles,
-                ctl + CTL_NCHUNK);
+    // 3. geometric blocks with their merge groups, and work chunks
+    const int stiles = cdiv(n1, SCAN_TILE);
+    hipLaunchKernelGGL(k_blocks_count, dim3(stiles), dim3(WG), 0, st, B.keys[cur], N, pack, stiles, B.scan_tiles);
+    hipLaunchKernelGGL(k_blocks_emit, dim3(stiles), dim3(WG), 0, st, B.keys[cur], N, pack, stiles, B.scan_tiles, B.gstart,
+                       B.gcode, B.group_start, ctl);
+    // (no more groups than particles, nor than slabs, or single blocks, of the padded dense grids)
+    const int slabs = pack ? nbricks / 4 + 1 : nbricks;
+    device_scan<1>(st, OpChunks{B.gstart, B.gcode, B.group_start, ctl, N, chunk, B.chunks, T}, N < slabs ? N : slabs,
+                   B.scan_tiles, ctl + CTL_NCHUNK);
     // 4. gather the whole particle state into (chunk-spread) sorted order
     hipLaunchKernelGGL(k_permute_chunks, dim3(2048), dim3(WG), 0, st, S_cur, S_alt, id_cur, id_alt, B.sorted_ids,
                        B.vals[cur], B.keys[cur], B.chunks, ctl, cap, spread, T.shift);
     // 5. physical blocks: 3x3x3 dilation, compacted in padded linear order
-    hipLaunchKernelGGL(k_fill, dim3(cdiv(nbricks, WG)), dim3(WG), 0, st, B.brick_state, 0, nbricks);
+    hipLaunchKernelGGL(k_clear2, dim3(cdiv(nbricks, WG)), dim3(WG), 0, st, B.brick_state, reg_n, nbricks);
     hipLaunchKernelGGL(k_dilate, dim3(512), dim3(WG), 0, st, B.gcode, ctl, T, B.brick_state);
     device_scan(st, OpActive{B.brick_state, B.active}, nbricks, B.scan_tiles, ctl + CTL_NACTIVE);
-    hipLaunchKernelGGL(k_mark_active, dim3(512), dim3(WG), 0, st, B.active, ctl, B.brick_state);
     // 6. tile registrations of the chunks with the physical blocks
-    hipLaunchKernelGGL(k_fill, dim3(cdiv(nbricks, WG)), dim3(WG), 0, st, reg_n, 0, nbricks);
     hipLaunchKernelGGL(k_register, dim3(1024), dim3(WG), 0, st, B.chunks, B.keys[cur], ctl, B.brick_state, reg_n, reg,
                        T);
     hipLaunchKernelGGL(k_sort_registrations, dim3(1024), dim3(WG), 0, st, ctl, reg_n, reg);
-    hipLaunchKernelGGL(k_finish_rebuild, dim3(1), dim3(1), 0, st, ctl);
     hipLaunchKernelGGL(k_rank_ends, dim3(1), dim3(WG), 0, st, B.keys[cur], N, B.gcode, B.chunks, B.active, ctl, T);
 }
 
