@@ -546,14 +546,19 @@ __device__ __forceinline__ void material_step(const Mat& M, float dt, int pendin
             // F_E' = U diag(sc/sig) U^T Fhat = Fhat + U diag(sc/sig - 1) U^T Fhat: the
             // rounding of U (orthogonal only to FP32 precision) then scales with the
             // plastic correction instead of adding strain noise to elastic states.
-            float R[6];
-            sym_from_eig(U, r[0], r[1], r[2], R);
+            // (not formed in a wave whose particles are all elastic)
 #pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                const float f0 = Fh[0 * 3 + b], f1 = Fh[1 * 3 + b], f2 = Fh[2 * 3 + b];
-                F[0 * 3 + b] = f0 + (R[0] * f0 + R[1] * f1 + R[2] * f2);
-                F[1 * 3 + b] = f1 + (R[1] * f0 + R[3] * f1 + R[4] * f2);
-                F[2 * 3 + b] = f2 + (R[2] * f0 + R[4] * f1 + R[5] * f2);
+            for (int i = 0; i < 9; ++i) F[i] = Fh[i];
+            if (__any(r[0] != 0.0f || r[1] != 0.0f || r[2] != 0.0f)) {
+                float R[6];
+                sym_from_eig(U, r[0], r[1], r[2], R);
+#pragma unroll
+                for (int b = 0; b < 3; ++b) {
+                    const float f0 = Fh[0 * 3 + b], f1 = Fh[1 * 3 + b], f2 = Fh[2 * 3 + b];
+                    F[0 * 3 + b] = f0 + (R[0] * f0 + R[1] * f1 + R[2] * f2);
+                    F[1 * 3 + b] = f1 + (R[1] * f0 + R[3] * f1 + R[4] * f2);
+                    F[2 * 3 + b] = f2 + (R[2] * f0 + R[4] * f1 + R[5] * f2);
+                }
             }
             const float Jc = sc[0] * sc[1] * sc[2];
             s = s * J / Jc;

@@ -32,22 +32,14 @@ struct Stencil {
 __device__ __forceinline__ bool make_stencil(const float x[3], const Step& P, Stencil& s, unsigned& err) {
     bool ok = true;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
+    for (int a = 0; a < 3; ++a) {  // (selects, no branches)
         const float t = x[a] * P.fn;
         const float b = floorf(t - 0.5f);
-        if (!(b == b)) {
-            err |= MPM_ERR_NONFINITE;
-            ok = false;
-            s.base[a] = 0;
-            s.f[a] = 1.0f;
-        } else {
-            if (!(b >= 0.0f && b <= (float)(P.n - 2))) {
-                err |= MPM_ERR_DOMAIN;
-                ok = false;
-            }
-            s.base[a] = (int)b;
-            s.f[a] = t - b;
-        }
+        const bool num = b == b, in = b >= 0.0f && b <= (float)(P.n - 2);
+        err |= in ? 0u : num ? MPM_ERR_DOMAIN : MPM_ERR_NONFINITE;
+        ok = ok && in;
+        s.base[a] = num ? (int)b : 0;
+        s.f[a] = num ? t - b : 1.0f;
         const float f = s.f[a];
         s.w[a][0] = 0.5f * (1.5f - f) * (1.5f - f);
         s.w[a][1] = 0.75f - (f - 1.0f) * (f - 1.0f);

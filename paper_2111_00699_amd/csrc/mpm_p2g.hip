@@ -378,7 +378,6 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, con
                     S[sidx(FX + a, p, cap)] = x[a];
                     fin = fin && (fabsf(x[a]) < 1e30f) && (fabsf(v[a]) < 1e30f);
                 }
-                left = left || left_free_zone(x, P.fn, B);
                 if (!fin) err |= MPM_ERR_NONFINITE;
             }
         }
@@ -421,12 +420,11 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, con
 #pragma unroll
             for (int a = 0; a < 3; ++a)
                 q[a] = M.mp * v[a] - (Ad[a * 3 + 0] * st.f[0] + Ad[a * 3 + 1] * st.f[1] + Ad[a * 3 + 2] * st.f[2]);
-            in_zone = ok;
+            bool zone = true;  // the cell code base + 1 within the particle's free zone [4B-3, 4B+6]
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const int l = st.base[a] - (4 * B[a] - 4);
-                in_zone = in_zone && l >= 0 && l <= TILE - 3;
-            }
+            for (int a = 0; a < 3; ++a) zone = zone && (unsigned)(st.base[a] - (4 * B[a] - 4)) <= (unsigned)(TILE - 3);
+            in_zone = ok && zone;
+            if constexpr (FUSED) left = left || !zone;
         } else {
 #pragma unroll
             for (int k = 0; k < 9; ++k) Ad[k] = 0.0f;
@@ -663,21 +661,42 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, con
             __syncthreads();
             const int nw = n_weak;  // uniform over the workgroup
             if (nw > 0) {
-                for (int k0 = 0; k0 < nw; k0 += 64) {
-                    const int mine = k0 + lane < nw ? weak[k0 + lane] : 0;
-                    for (int k = 0; k < min(64, nw - k0); ++k) {
-                        const int e = __builtin_amdgcn_readlane(mine, k);
-                        const int wx = e & 31, wy = (e >> 5) & 31, wz = e >> 10;
-                        const unsigned o0 = lo[0] + wx - st.base[0], o1 = lo[1] + wy - st.base[1], o2 = lo[2] + wz - st.base[2];
-                        if (!tiled || o0 > 2u || o1 > 2u || o2 > 2u) continue;
-                        double* node = tq + wx + R * wy + Q * wz;
-                        const double w = (double)(pick3(st.w[1], o1) * pick3(st.w[2], o2)) * (double)pick3(st.w[0], o0);
-                        unsafeAtomicAdd(node, w);
+                // Only a particle with a weight below the bound can have added to a weak node (its smallest
+                // weight is the product of its per-axis minima): about one lane per wave.  The wave takes
+                // such particles one by one and tests 64 weak nodes at a time, a lane each.
+                float wmin = 1.0f;
 #pragma unroll
-                        for (int a = 0; a < 3; ++a)
-                            unsafeAtomicAdd(node + (a + 1) * CT,
-                                            w * (double)(q[a] + (float)o1 * Ad[3 * a + 1] + (float)o2 * Ad[3 * a + 2] +
-                                                         (float)o0 * Ad[3 * a]));
+                for (int a = 0; a < 3; ++a) wmin *= fminf(fminf(st.w[a][0], st.w[a][1]), st.w[a][2]);
+                const unsigned long long tiny = __ballot(tiled && wmin < 0x1.01p-32f);
+                for (int k0 = 0; tiny && k0 < nw; k0 += 64) {
+                    const bool mine = k0 + lane < nw;
+                    const int e = mine ? weak[k0 + lane] : 0, wx = e & 31, wy = (e >> 5) & 31, wz = e >> 10;
+                    double* node = tq + wx + R * wy + Q * wz;
+                    for (unsigned long long m = tiny; m; m &= m - 1) {
+                        const int l = __builtin_ctzll(m);
+                        auto get = [&](float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
+                        const unsigned o0 = lo[0] + wx - __builtin_amdgcn_readlane(st.base[0], l);
+                        const unsigned o1 = lo[1] + wy - __builtin_amdgcn_readlane(st.base[1], l);
+                        const unsigned o2 = lo[2] + wz - __builtin_amdgcn_readlane(st.base[2], l);
+                        const bool hit = mine && o0 <= 2u && o1 <= 2u && o2 <= 2u;
+                        if (!__any(hit)) continue;
+                        float w[3][3], am[9], qm[3];
+#pragma unroll
+                        for (int k = 0; k < 9; ++k) {
+                            w[k / 3][k % 3] = get(st.w[k / 3][k % 3]);
+                            am[k] = get(Ad[k]);
+                        }
+#pragma unroll
+                        for (int a = 0; a < 3; ++a) qm[a] = get(q[a]);
+                        if (hit) {
+                            const double wt = (double)(pick3(w[1], o1) * pick3(w[2], o2)) * (double)pick3(w[0], o0);
+                            unsafeAtomicAdd(node, wt);
+#pragma unroll
+                            for (int a = 0; a < 3; ++a)
+                                unsafeAtomicAdd(node + (a + 1) * CT,
+                                                wt * (double)(qm[a] + (float)o1 * am[3 * a + 1] + (float)o2 * am[3 * a + 2] +
+                                                              (float)o0 * am[3 * a]));
+                        }
                     }
                 }
                 __syncthreads();
