@@ -42,6 +42,8 @@ using namespace mpm;
 namespace {
 
 constexpr int RING = 128;
+// Pinned words after the ring: a graph frame's rebuild request, its speeds, the error word of a read.
+constexpr int PIN_SPEED = RING + 1, PIN_ERROR = RING + 3, PIN_WORDS = RING + 4;
 constexpr int PROF_SLOTS = 4096;
 
 std::string g_create_error;
@@ -117,7 +119,7 @@ struct mpm_ctx {
     float auto_cfl = 0.0f, auto_dt_max = 0.0f;
     float* speed_dev = nullptr;  // [0..1]: the largest particle speed and the sum of speeds (auto dt,
                                  // exit horizon); [2..3]: the same, reduced at the end of each graph frame
-    bool graph_speed = false;    // ring[RING + 1 ..] holds the speeds at the end of the last frame
+    bool graph_speed = false;    // ring[PIN_SPEED ..] holds the speeds at the end of the last frame
 
     // profiling
     uint32_t prof_mask = 0;
@@ -508,16 +510,18 @@ void note_substep(mpm_ctx* c, int act) {
     ++c->parity_ctr;
 }
 
+int report_error_word(mpm_ctx* c, int word) {
+    if (!word) return MPM_OK;
+    char buf[96];
+    snprintf(buf, sizeof buf, "device error word 0x%x", (unsigned)word);
+    return fail(c, MPM_ESTATE, buf);
+}
+
 int check_error_word(mpm_ctx* c) {
     int h[CTL_WORDS];
     HIP_OK(c, hipMemcpyAsync(h, c->ctl, sizeof h, hipMemcpyDeviceToHost, c->stream));
     HIP_OK(c, hipStreamSynchronize(c->stream));
-    if (h[CTL_ERROR]) {
-        char buf[96];
-        snprintf(buf, sizeof buf, "device error word 0x%x", (unsigned)h[CTL_ERROR]);
-        return fail(c, MPM_ESTATE, buf);
-    }
-    return MPM_OK;
+    return report_error_word(c, h[CTL_ERROR]);
 }
 
 // Whether a substep may leave its G2P to the next substep's P2G (the fused
@@ -657,7 +661,7 @@ int record_frame_graph(mpm_ctx* c, int cur, bool rebuild, float frame_dt, const 
         enqueue_g2p(c->stream, c->L, T, c->S[buf], c->cap, c->B.chunks, c->ctl, c->G, flag, lds_box,
                     (ns[0] - 1) & 1, fb_limit(c), c->cfg.chunk, active_ranks(ns, 0), 1);
     // the speeds the next frame's exit horizon starts from
-    enqueue_speeds_to_host(c->stream, c->S[buf], c->cap, (int)c->N, c->speed_dev + 2, c->ring_dev + RING + 1);
+    enqueue_speeds_to_host(c->stream, c->S[buf], c->cap, (int)c->N, c->speed_dev + 2, c->ring_dev + PIN_SPEED);
     hipGraph_t graph = nullptr;
     const hipError_t e1 = hipGetLastError();
     const hipError_t e2 = hipStreamEndCapture(c->stream, &graph);
@@ -698,7 +702,7 @@ int current_mean_speed(mpm_ctx* c, double& v) {
     float w[2] = {0.0f, 0.0f};
     if (c->graph_speed) {
         for (int k = 0; k < 2; ++k) {
-            const int bits = __atomic_load_n(c->ring + RING + 1 + k, __ATOMIC_ACQUIRE);
+            const int bits = __atomic_load_n(c->ring + PIN_SPEED + k, __ATOMIC_ACQUIRE);
             memcpy(&w[k], &bits, sizeof(float));
         }
     } else {
@@ -949,13 +953,13 @@ int mpm_create(const mpm_config* cfg, mpm_ctx** out) {
         c->err = "initialisation failed";
         return bail(MPM_EDEVICE);
     }
-    if (hipHostMalloc(&c->ring, sizeof(int) * (RING + 3), hipHostMallocDefault) != hipSuccess ||
+    if (hipHostMalloc(&c->ring, sizeof(int) * PIN_WORDS, hipHostMallocDefault) != hipSuccess ||
         hipHostGetDevicePointer(reinterpret_cast<void**>(&c->ring_dev), c->ring, 0) != hipSuccess) {
         (void)hipGetLastError();
         c->err = "pinned ring allocation failed";
         return bail(MPM_ENOMEM);
     }
-    memset(c->ring, 0, sizeof(int) * (RING + 3));
+    memset(c->ring, 0, sizeof(int) * PIN_WORDS);
     for (int i = 0; i < RING; ++i)
         if (hipEventCreateWithFlags(&c->ev[i], hipEventDisableTiming) != hipSuccess) {
             c->err = "event creation failed";
@@ -1094,10 +1098,18 @@ int mpm_read_particles(mpm_ctx* c, int32_t scene, int64_t count, float* x, float
     // state read is the one the next P2G would use
     if (c->pending && c->sur_any && (F || s))
         if (int r = land_pending(c)) return r;
-    enqueue_read(c->stream, tables(c), c->S[c->cur], c->ids[c->cur], c->cap, (int)c->N, scene, (int)count, c->pending,
-                 x, v, C, F, s);
+    // The scenes' particles are stored scene after scene, by rank, until particles are added to the
+    // order of the last rebuild: then (and before the first rebuild) all of them are searched.
+    int j0 = 0, n = (int)c->N;
+    if (c->last_rebuild >= 0 && c->n_at_rebuild == c->N) {
+        for (int r = 0; r < c->table[scene].rank; ++r) j0 += (int)c->sh[c->rank_scene[r]].N;
+        n = (int)count;
+    }
+    enqueue_read(c->stream, tables(c), c->S[c->cur], c->ids[c->cur], c->cap, j0, n, scene, (int)count, c->pending, x, v, C,
+                 F, s, c->ctl, c->ring_dev + PIN_ERROR);
     HIP_OK(c, hipGetLastError());
-    return check_error_word(c);
+    HIP_OK(c, hipStreamSynchronize(c->stream));
+    return report_error_word(c, __atomic_load_n(c->ring + PIN_ERROR, __ATOMIC_ACQUIRE));
 }
 
 int mpm_read_grid(mpm_ctx* c, int32_t scene, float* m, float* v) {

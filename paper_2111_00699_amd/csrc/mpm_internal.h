@@ -268,8 +268,10 @@ void enqueue_materialize_map(hipStream_t st, const Launch& L, const Scenes& T, f
                              const Chunk* chunks, const int* ctl, int chunk);
 void enqueue_insert(hipStream_t st, float* S, int* ids, int64_t cap, int N0, int count, int scene, int id0,
                     const float* x, const float* v, const float* C, const float* F, const float* s, int* ctl);
-void enqueue_read(hipStream_t st, const Scenes& T, const float* S, const int* ids, int64_t cap, int N, int scene,
-                  int Ns, int pending, float* x, float* v, float* C, float* F, float* s);
+// The scene's Ns particles lie among the n storage positions from j0 on; host_err: pinned, takes the
+// device error word.
+void enqueue_read(hipStream_t st, const Scenes& T, const float* S, const int* ids, int64_t cap, int j0, int n, int scene,
+                  int Ns, int pending, float* x, float* v, float* C, float* F, float* s, const int* ctl, int* host_err);
 void enqueue_read_grid(hipStream_t st, const Scene& sc, const GridBuffers& G, int step, float* m, float* v);
 void query_launch(Launch& L, int chunk);
 

@@ -474,13 +474,20 @@ __global__ __launch_bounds__(WG) void k_insert(float* __restrict__ S, int* __res
     if (err) atomicOr(&ctl[CTL_ERROR], (int)err);
 }
 
-// Scatter the particles of one scene (Ns of them) to insertion order.
+// Scatter the particles of one scene (Ns of them), which lie among the n
+// storage positions from j0 on, to insertion order; the device error word goes
+// to pinned host memory with it (the stream orders it after every kernel that
+// could set it), which saves a read its copy.
 __global__ __launch_bounds__(WG) void k_read(const float* __restrict__ S, const int* __restrict__ ids, int64_t cap,
-                                             int N, int scene, int Ns, int pending, Scenes T, float* __restrict__ x,
-                                             float* __restrict__ v, float* __restrict__ C, float* __restrict__ F,
-                                             float* __restrict__ s) {
-    const int j = blockIdx.x * WG + threadIdx.x;
-    if (j >= N || fsid_scene(S[sidx(FSID, j, cap)]) != scene) return;
+                                             int j0, int n, int scene, int Ns, int pending, Scenes T,
+                                             float* __restrict__ x, float* __restrict__ v, float* __restrict__ C,
+                                             float* __restrict__ F, float* __restrict__ s,
+                                             const int* __restrict__ ctl, int* __restrict__ host_err) {
+    const int i = blockIdx.x * WG + threadIdx.x, j = j0 + i;
+    if (i == 0)
+        __hip_atomic_store(host_err, __hip_atomic_load(&ctl[CTL_ERROR], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (i >= n || fsid_scene(S[sidx(FSID, j, cap)]) != scene) return;
     const Scene& sc = T.scene[scene];
     const int64_t id = ids[j];
 #pragma unroll
@@ -673,11 +680,10 @@ void enqueue_insert(hipStream_t st, float* S, int* ids, int64_t cap, int N0, int
                        F, s, ctl);
 }
 
-void enqueue_read(hipStream_t st, const Scenes& T, const float* S, const int* ids, int64_t cap, int N, int scene,
-                  int Ns, int pending, float* x, float* v, float* C, float* F, float* s) {
-    if (N <= 0) return;
-    hipLaunchKernelGGL(k_read, dim3(cdiv(N, WG)), dim3(WG), 0, st, S, ids, cap, N, scene, Ns, pending, T, x, v, C, F,
-                       s);
+void enqueue_read(hipStream_t st, const Scenes& T, const float* S, const int* ids, int64_t cap, int j0, int n, int scene,
+                  int Ns, int pending, float* x, float* v, float* C, float* F, float* s, const int* ctl, int* host_err) {
+    hipLaunchKernelGGL(k_read, dim3(cdiv(n > 0 ? n : 1, WG)), dim3(WG), 0, st, S, ids, cap, j0, n, scene, Ns, pending, T, x,
+                       v, C, F, s, ctl, host_err);
 }
 
 void enqueue_read_grid(hipStream_t st, const Scene& sc, const GridBuffers& G, int step, float* m, float* v) {
