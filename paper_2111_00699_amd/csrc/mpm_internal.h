@@ -40,6 +40,19 @@ __host__ __device__ __forceinline__ int64_t sidx(int f, int64_t j, int64_t cap) 
 #endif
 }
 
+// Field f of particle p (p < 2^30): a base common to the wave (scalar registers) and a 32-bit byte
+// offset, the load's own addressing form, so that no lane adds 64-bit addresses (fused P2G of 1.39M snow
+// particles: 99.2 -> 96.9 us; the asm keeps the offset's widening in the load's own block).
+__device__ __forceinline__ float& field(float* S, int f, int p, int64_t cap) {
+#if MPM_AOSOA
+    return S[sidx(f, p, cap)];
+#else
+    uint32_t off = 4u * (uint32_t)p;
+    asm("" : "+v"(off));
+    return *reinterpret_cast<float*>(reinterpret_cast<char*>(S + f * cap) + off);
+#endif
+}
+
 __device__ __forceinline__ int fsid_scene(float f) { return __float_as_int(f) & 255; }
 __device__ __forceinline__ void fsid_block(float f, int B[3]) {
     const uint32_t u = (uint32_t)__float_as_int(f);

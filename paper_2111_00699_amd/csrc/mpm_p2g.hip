@@ -274,7 +274,7 @@ __device__ void snow_without_svd(const mlp::NetLds16* net, float* stage, const S
 // state up to date before a read recomputes them).  vel, host_flag and
 // fb_limit serve that G2P.
 template <bool GLOBAL_ONLY, int NT, int SURM, bool FUSED, bool F32 = false>
-__device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, const Chunk* __restrict__ chunks,
+__device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, const Chunk* __restrict__ chunks,
                                          int* __restrict__ ctl, float* __restrict__ acc,
                                          int* __restrict__ acc_dirty, float4* __restrict__ stage,
                                          int stage_nodes, int4* __restrict__ box, int* __restrict__ brick_state,
@@ -322,6 +322,8 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, con
     const int slice0 = slice * (int)blockIdx.x;
     int used = 0;
     for (int c = begin; c < end; c += stride) {
+        int64_t cap = cap_;  // opaque per chunk: hoisted, the fields' 27 bases spill scalar registers
+        asm("" : "+s"(cap));
         const Chunk ch = chunks[c];
         const Scene& sc = T.scene[ch.scene];
         const Step P = sc.P;
@@ -338,19 +340,19 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, con
         // (lanes past the chunk's end load its first particle: no branch and no defaults)
         float x[3], v[3] = {0.f, 0.f, 0.f}, C[9], F[9], s, tau[6];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) x[a] = S[sidx(FX + a, p, cap)];
+        for (int a = 0; a < 3; ++a) x[a] = field(S, FX + a, p, cap);
 #pragma unroll
-        for (int k = 0; k < 9; ++k) C[k] = FUSED ? 0.0f : S[sidx(FC + k, p, cap)];
+        for (int k = 0; k < 9; ++k) C[k] = FUSED ? 0.0f : field(S, FC + k, p, cap);
         if (!FUSED) {
 #pragma unroll
-            for (int a = 0; a < 3; ++a) v[a] = S[sidx(FV + a, p, cap)];
+            for (int a = 0; a < 3; ++a) v[a] = field(S, FV + a, p, cap);
         }
-        s = S[sidx(FS, p, cap)];
+        s = field(S, FS, p, cap);
         int B[3];  // the particle's block at the last rebuild (its free zone)
-        fsid_block(S[sidx(FSID, p, cap)], B);
+        fsid_block(field(S, FSID, p, cap), B);
         if (M.kind != MPM_WATER) {
 #pragma unroll
-            for (int k = 0; k < 9; ++k) F[k] = S[sidx(FF + k, p, cap)];
+            for (int k = 0; k < 9; ++k) F[k] = field(S, FF + k, p, cap);
         } else {
 #pragma unroll
             for (int k = 0; k < 9; ++k) F[k] = 0.0f;  // not used
@@ -375,7 +377,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, con
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
                     x[a] += dt * v[a];
-                    S[sidx(FX + a, p, cap)] = x[a];
+                    field(S, FX + a, p, cap) = x[a];
                     fin = fin && (fabsf(x[a]) < 1e30f) && (fabsf(v[a]) < 1e30f);
                 }
                 if (!fin) err |= MPM_ERR_NONFINITE;
@@ -403,9 +405,9 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap, con
             if (pending) {  // the deferred update of the last G2P lands here
                 if (M.kind != MPM_WATER) {
 #pragma unroll
-                    for (int k = 0; k < 9; ++k) S[sidx(FF + k, p, cap)] = F[k];
+                    for (int k = 0; k < 9; ++k) field(S, FF + k, p, cap) = F[k];
                 }
-                if (M.kind != MPM_JELLY) S[sidx(FS, p, cap)] = s;
+                if (M.kind != MPM_JELLY) field(S, FS, p, cap) = s;
             }
             ok = make_stencil(x, P, st, err);
 #if MPM_WEIGHTS_IN_LDS  // the register-pressure ablation: weights parked in LDS until the scatter
@@ -798,10 +800,10 @@ __global__ __launch_bounds__(NT) void k_materialize_map(float* __restrict__ S, i
         float C[9], F[9], s = 1.0f, tau[6];
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
-            C[k] = have ? S[sidx(FC + k, p, cap)] : 0.0f;
-            F[k] = have ? S[sidx(FF + k, p, cap)] : ((k % 4 == 0) ? 1.0f : 0.0f);
+            C[k] = have ? field(S, FC + k, p, cap) : 0.0f;
+            F[k] = have ? field(S, FF + k, p, cap) : ((k % 4 == 0) ? 1.0f : 0.0f);
         }
-        if (have) s = S[sidx(FS, p, cap)];
+        if (have) s = field(S, FS, p, cap);
         bool fb = false;
         if (sc.ret != 0 && M.kind == MPM_SNOW) {  // uniform over the workgroup
             if constexpr (SURM == 2) {
@@ -818,9 +820,9 @@ __global__ __launch_bounds__(NT) void k_materialize_map(float* __restrict__ S, i
         if (have) {
             if (M.kind != MPM_WATER) {
 #pragma unroll
-                for (int k = 0; k < 9; ++k) S[sidx(FF + k, p, cap)] = F[k];
+                for (int k = 0; k < 9; ++k) field(S, FF + k, p, cap) = F[k];
             }
-            if (M.kind != MPM_JELLY) S[sidx(FS, p, cap)] = s;
+            if (M.kind != MPM_JELLY) field(S, FS, p, cap) = s;
         }
     }
 }
