@@ -174,6 +174,20 @@ struct Scenes {
     int sur_any;             // 2: some scene runs the network; 1: some the closed form only; 0: none
 };
 
+// Scene i, the same in every lane, read through the scalar cache into scalar registers (no kernel
+// writes the table): as an ordinary load its 30 constants would take a vector register each.
+__device__ __forceinline__ Scene scene_of(const Scenes& T, int i) {
+    constexpr int W = sizeof(Scene) / 4;
+    static_assert(sizeof(Scene) % 4 == 0, "whole words");
+    struct Words {
+        uint32_t w[W];
+    } b;
+    const auto* src = (const __attribute__((address_space(4))) uint32_t*)(uintptr_t)(T.scene + __builtin_amdgcn_readfirstlane(i));
+#pragma unroll
+    for (int k = 0; k < W; ++k) b.w[k] = src[k];
+    return __builtin_bit_cast(Scene, b);
+}
+
 enum RankEnd : int { RE_PART = 0, RE_GBLOCK = 1, RE_CHUNK = 2, RE_ACTIVE = 3 };
 
 // Entries of kind k that belong to the first `act` ranks (act = S: all).
