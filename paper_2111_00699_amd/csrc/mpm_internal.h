@@ -208,6 +208,15 @@ __device__ __forceinline__ int rank_of_brick(const Scenes& T, int b) {
     return lo;
 }
 
+// Contiguous per-XCD ranges: workgroup w runs on XCD w % 8, so each XCD walks
+// its own contiguous slice of the block-sorted work list.
+__device__ __forceinline__ void xcd_split(int total, int& begin, int& end, int& stride) {
+    const int x = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    stride = gridDim.x >> 3;
+    begin = (int)(((int64_t)total * x) >> 3) + slot;
+    end = (int)(((int64_t)total * (x + 1)) >> 3);
+}
+
 // ------------------------------------------------------------ launchers
 // Binning and sorting (mpm_bin.hip).
 struct BinBuffers {

@@ -507,39 +507,99 @@ __global__ __launch_bounds__(WG) void k_insert(float* __restrict__ S, int* __res
     if (err) atomicOr(&ctl[CTL_ERROR], (int)err);
 }
 
-// Scatter the particles of one scene (Ns of them), which lie among the n
+// Sort (key, val) by key over the workgroup (bitonic; equal keys keep their places).  Partners 64 and 128
+// threads apart exchange through LDS (ex: WG pairs), nearer ones inside the wave.
+template <int SIZE = 2, int STRIDE = 1>
+__device__ __forceinline__ void sort_workgroup(int& key, int& val, int2* ex) {
+    const int t = threadIdx.x;
+    int2 o;
+    if constexpr (STRIDE >= 64) {
+        __syncthreads();
+        ex[t] = make_int2(key, val);
+        __syncthreads();
+        o = ex[t ^ STRIDE];
+    } else if constexpr (STRIDE == 32) {
+        o = make_int2(__shfl_xor(key, 32), __shfl_xor(val, 32));
+    } else {
+        o = make_int2(__builtin_amdgcn_ds_swizzle(key, (STRIDE << 10) | 31),
+                      __builtin_amdgcn_ds_swizzle(val, (STRIDE << 10) | 31));
+    }
+    const bool up = (t & SIZE) == 0, lower = (t & STRIDE) == 0;  // (SIZE = WG: one ascending run)
+    const bool take = up == lower ? o.x < key : o.x > key;
+    key = take ? o.x : key;
+    val = take ? o.y : val;
+    if constexpr (STRIDE > 1)
+        sort_workgroup<SIZE, STRIDE / 2>(key, val, ex);
+    else if constexpr (SIZE < WG)
+        sort_workgroup<2 * SIZE, SIZE>(key, val, ex);
+}
+
+// Copy the particles of one scene (Ns of them), which lie among the n
 // storage positions from j0 on, to insertion order; the device error word goes
 // to pinned host memory with it (the stream orders it after every kernel that
 // could set it), which saves a read its copy.
+// SORT: a workgroup first sorts its particles by insertion id, so that a wave's
+// lanes store to runs of neighbouring places.  An XCD takes a contiguous range,
+// so that the parts of a line meet in one L2 (504 -> 408 us at 3.1M particles).
+template <bool SORT>
 __global__ __launch_bounds__(WG) void k_read(const float* __restrict__ S, const int* __restrict__ ids, int64_t cap,
                                              int j0, int n, int scene, int Ns, int pending, Scenes T,
                                              float* __restrict__ x, float* __restrict__ v, float* __restrict__ C,
                                              float* __restrict__ F, float* __restrict__ s,
                                              const int* __restrict__ ctl, int* __restrict__ host_err) {
-    const int i = blockIdx.x * WG + threadIdx.x, j = j0 + i;
+    constexpr int FIELDS = FSID, ROUND = 13;
+    __shared__ float row[SORT ? ROUND * WG : 1];
+    int begin, end, stride;  // one group of WG positions a workgroup
+    xcd_split(gridDim.x, begin, end, stride);
+    const int i = begin * WG + threadIdx.x, j = j0 + i;
     if (i == 0)
         __hip_atomic_store(host_err, __hip_atomic_load(&ctl[CTL_ERROR], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    if (i >= n || fsid_scene(S[sidx(FSID, j, cap)]) != scene) return;
-    const Scene& sc = T.scene[scene];
-    const int64_t id = ids[j];
+    const bool have = i < n && fsid_scene(S[sidx(FSID, j, cap)]) == scene;
+    if (!SORT && !have) return;
+    int id = INT_MAX, from = threadIdx.x;
+    float q[FIELDS];
+    if (have) {
+        id = ids[j];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        if (x) x[a * (int64_t)Ns + id] = S[sidx(FX + a, j, cap)];
-        if (v) v[a * (int64_t)Ns + id] = S[sidx(FV + a, j, cap)];
+        for (int f = 0; f < FIELDS; ++f) q[f] = S[sidx(f, j, cap)];
+        if (pending && (F || s)) {
+            const Scene& sc = T.scene[scene];
+            float Cp[9], tau[6];
+#pragma unroll
+            for (int k = 0; k < 9; ++k) Cp[k] = q[FC + k];
+            material_step(sc.M, sc.P.dt, 1, Cp, q + FF, q[FS], tau);
+        }
     }
-    float Cp[9], Fp[9], sp = S[sidx(FS, j, cap)], tau[6];
+    auto put = [&](int f, float val) {
+        const int64_t at = id;
+        if (f == FS) {
+            if (s) s[at] = val;
+        } else {
+            float* out = f >= FF ? F : f >= FC ? C : f >= FV ? v : x;
+            const int k = f - (f >= FF ? FF : f >= FC ? FC : f >= FV ? FV : FX);
+            if (out) out[k * (int64_t)Ns + at] = val;
+        }
+    };
+    if constexpr (!SORT) {
 #pragma unroll
-    for (int k = 0; k < 9; ++k) {
-        Cp[k] = S[sidx(FC + k, j, cap)];
-        Fp[k] = S[sidx(FF + k, j, cap)];
-        if (C) C[k * (int64_t)Ns + id] = Cp[k];
+        for (int f = 0; f < FIELDS; ++f) put(f, q[f]);
+    } else {
+        sort_workgroup(id, from, reinterpret_cast<int2*>(row));
+#pragma unroll
+        for (int f0 = 0; f0 < FIELDS; f0 += ROUND) {
+            __syncthreads();
+            if (have) {
+#pragma unroll
+                for (int f = f0; f < f0 + ROUND && f < FIELDS; ++f) row[(f - f0) * WG + threadIdx.x] = q[f];
+            }
+            __syncthreads();
+            if (id != INT_MAX) {
+#pragma unroll
+                for (int f = f0; f < f0 + ROUND && f < FIELDS; ++f) put(f, row[(f - f0) * WG + from]);
+            }
+        }
     }
-    if (pending && (F || s)) material_step(sc.M, sc.P.dt, 1, Cp, Fp, sp, tau);
-    if (F)
-#pragma unroll
-        for (int k = 0; k < 9; ++k) F[k * (int64_t)Ns + id] = Fp[k];
-    if (s) s[id] = sp;
 }
 
 __global__ __launch_bounds__(WG) void k_read_grid(const float4* __restrict__ vel, const int* __restrict__ stamp,
@@ -715,10 +775,21 @@ void enqueue_insert(hipStream_t st, float* S, int* ids, int64_t cap, int N0, int
                        F, s, ctl);
 }
 
+// Reads of at least this many positions sort each group by insertion id.  A particle's 25 values land 4
+// bytes here and there: unsorted, a wave's store is 64 requests to the L2, whose rate bounds a large read.
+// Sorted, neighbours in a row of cells share theirs: 408 -> 234 us at 3.1M particles, 136 -> 90 at 1.39M, 21.8
+// -> 17.7 at 262K, the same 12.2 at 131K.  Below, one group's latency counts and the sort only adds to it:
+// 8.9 -> 9.5 us at 65K, 6.6 -> 8.2 at 30K.
+constexpr int READ_SORTED = 1 << 17;
 void enqueue_read(hipStream_t st, const Scenes& T, const float* S, const int* ids, int64_t cap, int j0, int n, int scene,
                   int Ns, int pending, float* x, float* v, float* C, float* F, float* s, const int* ctl, int* host_err) {
-    hipLaunchKernelGGL(k_read, dim3(cdiv(n > 0 ? n : 1, WG)), dim3(WG), 0, st, S, ids, cap, j0, n, scene, Ns, pending, T, x,
-                       v, C, F, s, ctl, host_err);
+    const dim3 grid(cdiv(n > 0 ? n : 1, 8 * WG) * 8);
+    if (n >= READ_SORTED)
+        hipLaunchKernelGGL(k_read<true>, grid, dim3(WG), 0, st, S, ids, cap, j0, n, scene, Ns, pending, T, x, v, C, F, s, ctl,
+                           host_err);
+    else
+        hipLaunchKernelGGL(k_read<false>, grid, dim3(WG), 0, st, S, ids, cap, j0, n, scene, Ns, pending, T, x, v, C, F, s, ctl,
+                           host_err);
 }
 
 void enqueue_read_grid(hipStream_t st, const Scene& sc, const GridBuffers& G, int step, float* m, float* v) {

@@ -1,0 +1,102 @@
+"""Storage order in and out: a state that is only sorted comes back bit for bit.
+
+A rebuild sorts and permutes the stored particles and a read copies them back
+to insertion order.  Particles at rest, without stress or gravity, also pass
+their substep unchanged (every sum is an exact zero), so x, F and s come back
+exactly at every size: around the sort's tiles (2048 keys), the size where
+it changes its tiles and its histogram (262144), and the size from which a
+read sorts each group of 256 by insertion id (131072).  Before a substep every
+field does.
+"""
+import numpy as np
+import pytest
+
+from paper_2111_00699_amd import scenes
+
+from .test_gpu_parity import gpu_state, make_sim, print_case
+
+pytestmark = pytest.mark.gpu
+FIELDS = ("x", "v", "C", "F", "s")
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.fail("a GPU test ran without a visible GPU")
+    return torch
+
+
+REST = dict(scenes.JELLY, E=0.0)
+
+
+def cloud(N, seed, moving=False):
+    x = scenes.uniform(seed, 3 * N, 0, 0.05, 0.95).reshape(3, -1).astype(np.float32)
+    st = {k: np.asarray(a, np.float32) for k, a in scenes.nontrivial_state(x, seed=seed + 1, kind="snow").items()}
+    if not moving:
+        st["v"], st["C"] = np.zeros_like(st["v"]), np.zeros_like(st["C"])
+    return st
+
+
+def add(sim, st, scene=0, mat=REST):
+    sim.add_particles(mat, st["x"], v=st["v"], C=st["C"], F=st["F"], s=st["s"], scene=scene)
+
+
+def assert_same(got, st):
+    for k in FIELDS:
+        assert np.array_equal(np.asarray(got[k]).reshape(-1), st[k].reshape(-1)), k
+
+
+@pytest.mark.parametrize("N", [1, 255, 257, 131071, 131072, 131073])
+def test_state_reads_back_before_a_substep(torch_cuda, N):
+    print_case("inserted_state", N=N)
+    st = cloud(N, 300 + N % 1000, moving=True)
+    sim = make_sim(torch_cuda, dict(n=64, dt=1e-5))
+    add(sim, st)
+    assert_same(gpu_state(sim), st)
+    sim.close()
+
+
+@pytest.mark.parametrize("chunk", [0, 64, 512])
+@pytest.mark.parametrize("N", [1, 255, 2047, 2048, 2049, 131071, 131073, 262143, 262144, 262145])
+def test_sorted_state_reads_back_exactly(torch_cuda, oracle, N, chunk):
+    print_case("sorted_state", N=N, chunk=chunk)
+    st = cloud(N, 300 + N % 1000)
+    sim = make_sim(torch_cuda, dict(n=64, dt=1e-5, gravity=(0, 0, 0)), chunk=chunk)
+    add(sim, st)
+    for _ in range(2):  # the second sorts the storage order of the first
+        sim.rebuild()
+        sim.substep(1)
+        assert_same(gpu_state(sim), st)
+    keys, _ = sim.read_binning()
+    assert np.array_equal(keys, oracle.bin_particles(st["x"], 64)["sorted"])
+    sim.close()
+
+
+@pytest.mark.parametrize("sizes", [(1, 700, 3), (5000, 131072, 300)])
+def test_scene_reads_cover_their_storage(torch_cuda, sizes):
+    from paper_2111_00699_amd import mpm
+
+    print_case("scene_reads", sizes=sizes)
+    # (storage order is by rank: the last scene has the smallest dt)
+    descs = [dict(n=64, dt=(3 - k) * 1e-5, bc="sticky") for k in range(3)]
+    sim = mpm.Sim(64, 1e-5, scenes=descs, gravity=(0, 0, 0))
+    sts = [cloud(N, 400 + k) for k, N in enumerate(sizes)]
+    for k, st in enumerate(sts):
+        add(sim, st, scene=k)
+
+    def check():
+        for k, st in enumerate(sts):
+            assert_same({f: t.cpu().numpy() for f, t in sim.read_particles(scene=k).items()}, st)
+
+    check()  # insertion order
+    sim.substep(1)
+    check()  # sorted
+    extra = cloud(257, 500)
+    add(sim, extra, scene=0, mat=None)
+    sts[0] = {f: np.concatenate([sts[0][f].reshape(-1, sizes[0]), extra[f].reshape(-1, 257)], axis=1) for f in FIELDS}
+    check()  # appended behind the sorted ones
+    sim.substep(1)
+    check()
+    sim.close()
