@@ -437,6 +437,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
         int nt = 0, off = 0, R = 4, Q = 8;  // tight node count, staging offset, LDS pitches
         float m_bound = 0.0f;  // K, above every |m| of the chunk
         int em = 0;            // 27/64 (m + K) < 2^em: momentum units are 2^(em - FRAC_M)
+        int copies = 1;        // of the tile, an odd number of nodes apart (different banks)
         if (GLOBAL_ONLY && tid == 0) box[c] = make_int4(0, 0, 0, 0);
         if (!GLOBAL_ONLY) {
             const bool in_tile = have && in_zone;
@@ -500,7 +501,19 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
             if (!ch.tile) nt = -1;  // a registration list was full at the rebuild
             if (nt < 0 && tid == 0) atomicAdd(&ctl64(ctl, blockIdx.x)[CTL64_FALLBACK_CHUNKS], 1ull);
             off = slice0 + used;
-            if (nt > 0) used += nt;
+            if (nt > 0) {
+                used += nt;
+                // Lanes of one cell add to the same words, one after another: where the chunk holds 8
+                // particles and more per cell of its box, the tile is kept in up to 16 copies that the
+                // lanes take in turn.  (Water that ASFLIP has pressed into a corner holds thousands of
+                // particles in one cell: 48.4 -> 23.8 us at 143K.  From 4 a cell on it would be 22.3
+                // there, but 97.9 -> 105.3 for 1.39M snow particles, 8 to a cell, whose deal over the
+                // lanes already keeps a cell's particles apart.)
+                const int cells = (ext[0] - 2) * (ext[1] - 2) * (ext[2] - 2);
+                if (8 * cells <= count)
+                    while (copies < 16 && 4 * copies * cells <= count && 2 * copies * (Q * ext[2] | 1) <= CT) copies *= 2;
+                copies = __builtin_amdgcn_readfirstlane(copies);
+            }
             // (the tile is all zero here: cleared at the start, and every node a chunk touched is
             // zeroed again as it is stored)
             if (tid == 0)
@@ -534,7 +547,8 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
             for (int a = 0; a < 3; ++a) wmin *= fminf(fminf(st.w[a][0], st.w[a][1]), st.w[a][2]);
             const bool any_tiny = __any(tiled && wmin < TINY_W);
             if (tiled) {
-                tb = (st.base[0] - lo[0]) + R * (st.base[1] - lo[1]) + Q * (st.base[2] - lo[2]);
+                tb = (st.base[0] - lo[0]) + R * (st.base[1] - lo[1]) + Q * (st.base[2] - lo[2]) +
+                     (copies > 1 ? (tid & (copies - 1)) * (Q * ext[2] | 1) : 0);
                 unsigned long long* tu = reinterpret_cast<unsigned long long*>(tq);
                 const float m_scale = ldexpf(1.0f, FRAC_M_F32 - em), m_unit = ldexpf(1.0f, em - FRAC_M_F32);
                 float qs[3], As[9];  // in momentum units (exact: a power-of-two scale)
@@ -585,7 +599,8 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
                     scatter(std::false_type{});
             }
         } else if (tiled) {
-            tb = (st.base[0] - lo[0]) + R * (st.base[1] - lo[1]) + Q * (st.base[2] - lo[2]);
+            tb = (st.base[0] - lo[0]) + R * (st.base[1] - lo[1]) + Q * (st.base[2] - lo[2]) +
+                     (copies > 1 ? (tid & (copies - 1)) * (Q * ext[2] | 1) : 0);
             unsigned long long* tu = reinterpret_cast<unsigned long long*>(tq);
             // weights times DENORM_SPLIT (in the z weights), momentum with the rest of the scale
             double wx[3], wy[3], wz[3], ax[3], ay[3], az[3], mz[3];
@@ -632,6 +647,22 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
         // ---- store the tile to the chunk's staging slot
         if (!GLOBAL_ONLY) {
             __syncthreads();
+            if (copies > 1) {  // (whole-number sums: the same in any order)
+                unsigned long long* tu = reinterpret_cast<unsigned long long*>(tq);
+                const int nodes = Q * ext[2];
+                for (int t = tid; t < nodes; t += NT)
+#pragma unroll
+                    for (int ch4 = 0; ch4 < 4; ++ch4) {
+                        unsigned long long sum = tu[ch4 * CT + t];
+                        for (int k = 1; k < copies; ++k) {
+                            unsigned long long& w = tu[ch4 * CT + t + k * (nodes | 1)];
+                            sum += w;
+                            w = 0ull;
+                        }
+                        tu[ch4 * CT + t] = sum;
+                    }
+                __syncthreads();
+            }
             float4* slot = stage + off;
             const int e01 = ext[0] * ext[1];
             const float r01 = 1.0f / (float)(e01 > 0 ? e01 : 1), r0 = 1.0f / (float)(ext[0] > 0 ? ext[0] : 1);
