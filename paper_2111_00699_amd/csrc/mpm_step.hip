@@ -133,12 +133,21 @@ __global__ __launch_bounds__(WG) void k_grid(float* __restrict__ acc, int* __res
                                              const int* __restrict__ reg, const float4* __restrict__ stage,
                                              int zero_node, const int4* __restrict__ box, int parity, int nbricks,
                                              Scenes T, int act) {
+    // (the lists have an entry per brick of the context: a wave's first is loaded without waiting for
+    // their lengths)
+    const int lane = threadIdx.x & 63;
+    const int nwaves = gridDim.x * (WG / 64);
+    int it = blockIdx.x * (WG / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int b_nx = 0, m_nx = 0, r_nx = 0;
+    if (it < nbricks) {
+        b_nx = active[it];
+        m_nx = reg_n[it];
+        r_nx = reg[(int64_t)it * REG_MAX + lane];
+    }
     const int nact = rank_limit(T, ctl, act, RE_ACTIVE, CTL_NACTIVE);
     const int total = nact + min(ctl[CTL_OVF + parity], nbricks - ctl[CTL_NACTIVE]);
     const int step = ctl[CTL_STEP];
-    const int lane = threadIdx.x & 63;
     const int lx = lane & 3, ly = (lane >> 2) & 3, lz = lane >> 4;
-    const int nwaves = gridDim.x * (WG / 64);
     float4* acc4 = reinterpret_cast<float4*>(acc);
     // The blocks of a wave are a software pipeline: the block index, the registration count
     // and this lane's first registration of the next block are loaded as the current block
@@ -147,13 +156,13 @@ __global__ __launch_bounds__(WG) void k_grid(float* __restrict__ acc, int* __res
     // tiles is not paid in full per block.  (Every read is in bounds: reg holds REG_MAX
     // entries per block index, and box is read only for a registration that exists.)
     const bool one = T.S == 1;
-    int it = blockIdx.x * (WG / 64) + (threadIdx.x >> 6);
-    int b_nx = 0, m_nx = 0, r_nx = 0, dirty_nx = 0;
+    int dirty_nx = 0;
     int4 bb_nx = make_int4(0, 0, 0, 0);
     if (it < total) {
-        b_nx = it < nact ? active[it] : ovf[it - nact];
-        m_nx = it < nact ? reg_n[it] : 0;
-        r_nx = reg[(int64_t)it * REG_MAX + lane];
+        if (it >= nact) {
+            b_nx = ovf[it - nact];
+            m_nx = 0;
+        }
         if (lane < m_nx) bb_nx = box[r_nx];
         dirty_nx = acc_dirty[__builtin_amdgcn_readfirstlane(b_nx)];
     }
