@@ -66,7 +66,7 @@ constexpr int CT = 1024;  // LDS tile capacity in nodes (padded layout, below)
 // this kernel at scenes of a million particles (84% busy before), the longest
 // workgroup at small ones.  Fused P2G before and after: 109.6 -> 101.6 us on
 // snow of 1.39M particles, 259 -> 244 us on sand of 3.1M, 16.5 -> 14.4 us on
-// jelly of 32K.
+// jelly of 32K (96.5, 228 and 11.5 to 12.2 with what else has changed since).
 constexpr int FRAC_W = 54;  // weight: w <= 27/64, below 2^53 units; 512 of them below 2^62
 constexpr int FRAC_M = 53;  // momentum: w (m + K) scaled below 2^53 units
 constexpr double DENORM_SPLIT = 0x1p-1000;  // the weights' share of the scale into the denormal range
@@ -86,7 +86,7 @@ constexpr unsigned long long WEAK_SUM = 1ull << (FRAC_W - 32);
 // velocity sends some particles of a frame another way (of 142K fountain
 // particles about 60 in 44 substeps, J then off by up to 2e-3): there results
 // stay comparable from build to build only with the same rounding.  It costs
-// about 2 of that scene's 20 us per launch.
+// about 2 us per launch.
 constexpr float W_SCALE_F32 = 0x1p51f;
 constexpr int FRAC_M_F32 = 50;
 constexpr float TINY_W = 0x1p-32f;
