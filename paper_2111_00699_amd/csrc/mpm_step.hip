@@ -557,7 +557,7 @@ __global__ __launch_bounds__(WG) void k_read(const float* __restrict__ S, const 
                                              float* __restrict__ F, float* __restrict__ s,
                                              const int* __restrict__ ctl, int* __restrict__ host_err) {
     constexpr int FIELDS = FSID, ROUND = 13;
-    __shared__ float row[SORT ? ROUND * WG : 1];
+    __shared__ __align__(8) float row[SORT ? ROUND * WG : 2];  // (also the sort's pairs)
     int begin, end, stride;  // one group of WG positions a workgroup
     xcd_split(gridDim.x, begin, end, stride);
     const int i = begin * WG + threadIdx.x, j = j0 + i;
