@@ -70,13 +70,24 @@ constexpr int CT = 1024;  // LDS tile capacity in nodes (padded layout, below)
 constexpr int FRAC_W = 54;  // weight: w <= 27/64, below 2^53 units; 512 of them below 2^62
 constexpr int FRAC_M = 53;  // momentum: w (m + K) scaled below 2^53 units
 constexpr double DENORM_SPLIT = 0x1p-1000;  // the weights' share of the scale into the denormal range
-// A node whose weight sum in the tile is below this (2^-32) would be resolved
-// to too few units for its velocity (momentum / mass): the tile store lists
-// it, and its particles add to it again, in FP64 and unscaled.  The sum
-// decides, not the single contribution: about one particle in 70 has a
-// weight below 2^-32 somewhere in its stencil (59% of the waves), but only a
-// node at the very edge of a chunk's material has no other contribution.
-constexpr unsigned long long WEAK_SUM = 1ull << (FRAC_W - 32);
+// A weight below LIGHT_W (2^-32) is resolved to too few units by itself, and
+// the roundings of many such terms need not cancel (a plane of particles just
+// beyond a cell edge: all equal).  A node of the tile that holds some is good
+// to a few FP32 roundings all the same where its weight sum is at least 2^-33
+// for each of the chunk's L particles that have such a weight anywhere in
+// their stencil: its light terms, good to half a unit each, are then off by
+// 2^-22 of the sum together, its others by 2^-23 of themselves.  A node below
+// that (L << WEAK_SHIFT units) is weak: the tile store lists it, and its
+// particles add to it again, in FP64 and unscaled.  About one particle in 70
+// has a light weight (59% of the waves), but only a node at the very edge of a
+// chunk's material has no other contribution: without light particles no node
+// is weak, with the usual four of a chunk few are (runs of 32K to 3.1M
+// particles take 0.1% to 0.5% longer than with a bound of 2^-32 for any L,
+// which left equal terms' roundings at up to 9e-5 of a node's mass).
+// One particle in 4 10^4 has a weight that may round to nothing: it adds one
+// unit more to its nodes, so that a node that only such weights reach shows.
+constexpr float LIGHT_W = 0x1.01p-32f;  // (with room for the rounding of a product of FP32 weights)
+constexpr int WEAK_SHIFT = FRAC_W - 33;
 
 // Contexts with an ASFLIP scene keep FP32 terms (F32 below): the products w
 // and w m are rounded to FP32, then to units of 2^-51 (weight) and 2^(em - 50)
@@ -284,7 +295,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
     static_assert(!F32 || (!GLOBAL_ONLY && !FUSED), "FP32 terms: the separate tile path");
     static_assert(!FUSED || (!GLOBAL_ONLY && SURM == 0), "the fused G2P needs the LDS tile and the exact map");
     __shared__ __align__(16) double tq[GLOBAL_ONLY ? 1 : 4 * CT];
-    __shared__ int red_i[7][NT / 64];
+    __shared__ int red_i[8][NT / 64];
     // weak nodes of the tile: their box coordinates, 5 bits an axis (a box spans at most 16 nodes:
     // the reach of one 2x2x1 slab of blocks)
     __shared__ unsigned short weak[GLOBAL_ONLY ? 1 : CT];
@@ -467,6 +478,14 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
         float m_bound = 0.0f;  // K, above every |m| of the chunk
         int em = 0;            // 27/64 (m + K) < 2^em: momentum units are 2^(em - FRAC_M)
         int copies = 1;        // of the tile, an odd number of nodes apart (different banks)
+        int lights = 0;        // the chunk's particles with a weight below LIGHT_W
+        // the smallest of a stencil's 27 weights is the product of its per-axis minima
+        auto smallest_weight = [&] {
+            float w = 1.0f;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) w *= fminf(fminf(st.w[a][0], st.w[a][1]), st.w[a][2]);
+            return w;
+        };
         if (GLOBAL_ONLY && tid == 0) box[c] = make_int4(0, 0, 0, 0);
         if (!GLOBAL_ONLY) {
             const bool in_tile = have && in_zone;
@@ -485,6 +504,8 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
                     mb = fmaxf(mb, fabsf(q[a]) + 2.0f * (fabsf(Ad[3 * a]) + fabsf(Ad[3 * a + 1]) + fabsf(Ad[3 * a + 2])));
             }
             const int mbw = wave_max(__float_as_int(mb));
+            int light_w = 0;
+            if constexpr (!F32) light_w = (int)__popcll(__ballot(in_tile && smallest_weight() < LIGHT_W));
             if (lane == 0) {
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
@@ -492,6 +513,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
                     red_i[3 + a][wv] = mx[a];
                 }
                 red_i[6][wv] = mbw;
+                red_i[7][wv] = light_w;
             }
             __syncthreads();
             if constexpr (FUSED) {  // every gather is done: clear the staged node box, keeping the tile zero
@@ -512,6 +534,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
                     hi[a] = max(hi[a], red_i[3 + a][k]);
                 }
                 mbk = max(mbk, red_i[6][k]);
+                if constexpr (!F32) lights += __builtin_amdgcn_readfirstlane(red_i[7][k]);
             }
             // the chunk's momentum bound, above the rounding of the particles' own bounds and of m, and
             // its scale: every contribution w (m + K) <= 27/64 2 K < 2^em
@@ -569,12 +592,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
         const bool tiled = !GLOBAL_ONLY && have && ok && in_zone && nt > 0;
         int tb = 0;  // tile index of the stencil's first node
         if constexpr (F32) {
-            // Lanes whose stencil holds a weight below TINY_W; the smallest of a stencil's 27 weights is
-            // the product of its per-axis minima.
-            float wmin = 1.0f;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) wmin *= fminf(fminf(st.w[a][0], st.w[a][1]), st.w[a][2]);
-            const bool any_tiny = __any(tiled && wmin < TINY_W);
+            const bool any_tiny = __any(tiled && smallest_weight() < TINY_W);
             if (tiled) {
                 tb = (st.base[0] - lo[0]) + R * (st.base[1] - lo[1]) + Q * (st.base[2] - lo[2]) +
                      (copies > 1 ? (tid & (copies - 1)) * (Q * ext[2] | 1) : 0);
@@ -635,6 +653,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
             double wx[3], wy[3], wz[3], ax[3], ay[3], az[3], mz[3];
             const float ms = ldexpf(1.0f, FRAC_M - 74 - em);  // 2^(FRAC_M - em - 1074) / DENORM_SPLIT
             const double k = (double)m_bound * (double)ms;
+            const double mark = smallest_weight() <= 0x1p-54f ? 0x1p-1074 : 0.0;  // (one unit)
 #pragma unroll
             for (int o = 0; o < 3; ++o) {
                 wx[o] = (double)st.w[0][o];
@@ -657,8 +676,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
                     for (int o0 = 0; o0 < 3; ++o0) {
                         const double w = wyz * wx[o0];
                         const int t = row + o0;
-                        // (one unit more, so that a node every weight of which rounds to nothing shows)
-                        atomicAdd(&tu[t], (unsigned long long)__double_as_longlong(fma(w, 0x1p-20, 0x1p-1074)));
+                        atomicAdd(&tu[t], (unsigned long long)__double_as_longlong(fma(w, 0x1p-20, mark)));
 #pragma unroll
                         for (int a = 0; a < 3; ++a) {
                             atomicAdd(&tu[(a + 1) * CT + t], (unsigned long long)__double_as_longlong(w * m[a]));
@@ -697,6 +715,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
             const float r01 = 1.0f / (float)(e01 > 0 ? e01 : 1), r0 = 1.0f / (float)(ext[0] > 0 ? ext[0] : 1);
             const double m_unit = ldexp(1.0, em - FRAC_M), mass_unit = 0x1p-54 * (double)M.mp;
             const double k_unit = 0x1p-54 * (double)m_bound;
+            const unsigned long long weak_sum = (unsigned long long)lights << WEAK_SHIFT;
             for (int u = tid; u < nt; u += NT) {  // staged in the tight box layout
                 const int z = div_small(u, r01), u01 = u - z * e01;
                 const int y = div_small(u01, r0), xx = u01 - y * ext[0];
@@ -709,7 +728,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
                                           (float)((double)(long long)tu[CT + t] * mu),
                                           (float)((double)(long long)tu[2 * CT + t] * mu),
                                           (float)((double)(long long)tu[3 * CT + t] * mu));
-                } else if (wsum == 0ull || wsum >= WEAK_SUM) {
+                } else if (wsum == 0ull || wsum >= weak_sum) {
                     const double wd = (double)wsum, kw = k_unit * wd;  // K times the weight sum
                     slot[u] = make_float4((float)(wd * mass_unit), (float)((double)tu[CT + t] * m_unit - kw),
                                           (float)((double)tu[2 * CT + t] * m_unit - kw),
@@ -723,13 +742,11 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
             __syncthreads();
             const int nw = n_weak;  // uniform over the workgroup
             if (nw > 0) {
-                // Only a particle with a weight below the bound can have added to a weak node (its smallest
-                // weight is the product of its per-axis minima): about one lane per wave.  The wave takes
-                // such particles one by one and tests 64 weak nodes at a time, a lane each.
-                float wmin = 1.0f;
-#pragma unroll
-                for (int a = 0; a < 3; ++a) wmin *= fminf(fminf(st.w[a][0], st.w[a][1]), st.w[a][2]);
-                const unsigned long long tiny = __ballot(tiled && wmin < 0x1.01p-32f);
+                // Only a particle with a weight below the weak nodes' bound can have added to one: a few
+                // lanes of a wave.  The wave takes such particles one by one and tests 64 weak nodes at a
+                // time, a lane each.
+                const float bound = (float)lights * (0.5f * LIGHT_W);
+                const unsigned long long tiny = __ballot(tiled && smallest_weight() < bound);
                 for (int k0 = 0; tiny && k0 < nw; k0 += 64) {
                     const bool mine = k0 + lane < nw;
                     const int e = mine ? weak[k0 + lane] : 0, wx = e & 31, wy = (e >> 5) & 31, wz = e >> 10;

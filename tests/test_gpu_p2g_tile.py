@@ -71,3 +71,71 @@ def test_nodes_reached_by_tiny_weights_only(torch_cuda, oracle, per_cluster, chu
         assert np.all(gm[om == 0.0] == 0.0)
         vv, oo = gv.reshape(3, -1)[:, seen], ov.reshape(3, -1)[:, seen]
         assert np.abs(vv - oo).max() <= TOL * np.abs(oo).max()
+
+
+def plane_particles(n, count, seed, others):
+    """Sites of `count` particles in one cell, each in a chunk of its own: all of a site's particles sit
+    the same 2^-15 .. 2^-19 of a cell above a cell edge along one axis (exact in FP32: below cell 16) and
+    anywhere in the cell along the other two.  The first `others` of them sit farther from the edge, 2^-10
+    .. 2^-14, so that the site's outer nodes hold a few larger weights beside the many."""
+    out = []
+    for a in range(3):
+        for k in range(5):
+            u = scenes.uniform(seed, 3 * count, 5 * a + k, 0.1, 0.9).reshape(count, 3)
+            u[:, a] = 2.0 ** -(15 + k)
+            u[:others, a] = 2.0 ** -(10 + (3 * k + np.arange(others)) % 5)
+            site = np.zeros(3)
+            site[[a, (a + 1) % 3, (a + 2) % 3]] = 10, 14 + 9 * k, 40
+            out.append((site + 0.5 + u) / n)
+    x = np.ascontiguousarray(np.concatenate(out).T.astype(np.float32))
+    assert all(np.any(np.float64(x[a]) * n == 10.5 + 2.0 ** -19) for a in range(3))
+    return x
+
+
+# A plane's outer nodes collect many equal weights, each far below 2^-32, to any sum.  Bars, all of FP32
+# roundings (2^-24 = u): a weight is a product of three quadratics of exact offsets (at most 4 u each and
+# 2 u for the products), a tile's sum is stored in FP32 and the grid update adds at most 8 tiles (9 u more):
+# 23 u, so 32 u of a node's own mass.  A velocity's numerator sums m = q + Ad o of nine FP32 terms, each up to
+# the chunk's largest S (per mass): 9 u S; the weights' errors weigh the particles anew, at most 2 * 14 u S;
+# storing and dividing take 9 u S: 46 u, so 64 u of S, which is far above the nodes' own velocities here.
+@pytest.mark.parametrize("count,chunk", [(64, 64), (128, 256), (256, 256), (512, 512), (512, 256)])
+@pytest.mark.parametrize("moving", [True, False])
+@pytest.mark.parametrize("others", [0, 3])
+def test_nodes_of_many_equal_tiny_weights(torch_cuda, oracle, count, chunk, moving, others):
+    n, u = 64, 2.0 ** -24
+    x = plane_particles(n, count, 900 + count, others)
+    N = x.shape[1]
+    st = dict(x=x, v=np.zeros((3, N), np.float32), C=np.zeros((9, N), np.float32),
+              F=np.repeat(np.eye(3, dtype=np.float32).reshape(9, 1), N, axis=1))
+    if moving:
+        st["v"] = scenes.uniform(17, 3 * N, 0, -1.0, 1.0).reshape(3, N).astype(np.float32)
+        st["C"] = scenes.uniform(17, 9 * N, 1, -400.0, 400.0).reshape(9, N).astype(np.float32)
+    # no stress (E = 0) and no gravity; the second substep of particles at rest is the fused kernel's
+    steps = 1 if moving else 2
+    mat = dict(scenes.JELLY, E=0.0)
+    cfg = dict(n=n, dt=1e-5, bc="separate", bc_cells=3, gravity=(0.0, 0.0, 0.0))
+    print_case("tiny_weight_planes", N=N, count=count, chunk=chunk, moving=moving, others=others)
+    sim = make_sim(torch_cuda, cfg, chunk=chunk)
+    sim.add_particles(mat, st["x"], v=st["v"], C=st["C"], F=st["F"])
+    sim.substep(steps)
+    assert sim.stats()["p2g_global_particles"] == 0
+    gm, gv = (t.cpu().numpy() for t in sim.read_grid())
+    sim.close()
+    _, om, ov, bad = oracle.substep(cfg, mat, st, steps=1)
+    assert bad == 0
+    seen = om > 0.0
+    light = seen & (om < 2.0 ** -20 * mat["rho"] / mat["ppc"] / n ** 3)
+    assert light.sum() >= 15 * 9  # every plane's nine outer nodes
+    em = np.abs(gm[seen] / om[seen] - 1.0).max()
+    print(f"[errs] mass {em / u:.1f} u", flush=True)
+    assert em <= 32 * u
+    if moving:
+        f = np.float64(x) * n - np.floor(np.float64(x) * n - 0.5)
+        C = np.float64(st["C"]).reshape(3, 3, N) / n
+        S = (np.abs(st["v"] - np.einsum("abp,bp->ap", C, f)) + 2 * np.abs(C).sum(axis=1)).max()
+        ev = np.abs(gv.reshape(3, -1)[:, seen] - ov.reshape(3, -1)[:, seen]).max()
+        print(f"[errs] velocity {ev / (u * S):.1f} u S, S {S:.1f}, largest light |v| "
+              f"{np.abs(ov.reshape(3, -1)[:, light]).max():.2f}", flush=True)
+        assert ev <= 64 * u * S
+    else:
+        assert np.all(gv == 0.0)
