@@ -89,15 +89,15 @@ constexpr double DENORM_SPLIT = 0x1p-1000;  // the weights' share of the scale i
 constexpr float LIGHT_W = 0x1.01p-32f;  // (with room for the rounding of a product of FP32 weights)
 constexpr int WEAK_SHIFT = FRAC_W - 33;
 
-// Contexts with an ASFLIP scene keep FP32 terms (F32 below): the products w
-// and w m are rounded to FP32, then to units of 2^-51 (weight) and 2^(em - 50)
-// (momentum) as two's complement words, and a term of weight below 2^-32
-// goes to the node's global accumulator.  ASFLIP's position share jumps where
-// a particle's volume change crosses 1, so any other rounding of a node
-// velocity sends some particles of a frame another way (of 142K fountain
-// particles about 60 in 44 substeps, J then off by up to 2e-3): there results
-// stay comparable from build to build only with the same rounding.  It costs
-// about 2 us per launch.
+// Contexts with an ASFLIP scene keep FP32 terms (F32 below), whatever map
+// their snow scenes take: the products w and w m are rounded to FP32, then to
+// units of 2^-51 (weight) and 2^(em - 50) (momentum) as two's complement
+// words, and a term of weight below 2^-32 goes to the node's global
+// accumulator.  ASFLIP's position share jumps where a particle's volume change
+// crosses 1, so any other rounding of a node velocity sends some particles of
+// a frame another way (of 142K fountain particles about 60 in 44 substeps, J
+// then off by up to 2e-3): there results stay comparable from build to build
+// only with the same rounding.  It costs about 2 us per launch.
 constexpr float W_SCALE_F32 = 0x1p51f;
 constexpr int FRAC_M_F32 = 50;
 constexpr float TINY_W = 0x1p-32f;
@@ -919,9 +919,9 @@ __global__ __launch_bounds__(NT) void k_p2g(MPM_P2G_PARAMS) {
     p2g_body<GLOBAL_ONLY, NT, SURM, false>(MPM_P2G_ARGS);
 }
 
-template <int NT>
+template <int NT, int SURM>
 __global__ __launch_bounds__(NT) void k_p2g_f32(MPM_P2G_PARAMS) {
-    p2g_body<false, NT, 0, false, true>(MPM_P2G_ARGS);
+    p2g_body<false, NT, SURM, false, true>(MPM_P2G_ARGS);
 }
 
 // The fused form holds the gathered v and C beside the P2G state; four
@@ -969,16 +969,23 @@ void enqueue_p2g(hipStream_t st, const Launch& L, const Scenes& T, float* S, int
         else if (nt == 256) launch(k_p2g<GO, 256, SU>, 256);                                   \
         else launch(k_p2g<GO, 512, SU>, 512);                                                  \
     } while (0)
+#define MPM_LAUNCH_P2G_F32_NT(SU)                                                              \
+    do {                                                                                       \
+        if (nt == 128) launch(k_p2g_f32<128, SU>, 128);                                        \
+        else if (nt == 256) launch(k_p2g_f32<256, SU>, 256);                                   \
+        else launch(k_p2g_f32<512, SU>, 512);                                                  \
+    } while (0)
     if (fused) {  // callers check: tile path, exact map
         if (nt == 128) launch(k_p2g_fused<128>, 128); else if (nt == 256) launch(k_p2g_fused<256>, 256); else launch(k_p2g_fused<512>, 512);
-    } else if (f32 && !global_atomics && surm == 0) {
-        if (nt == 128) launch(k_p2g_f32<128>, 128); else if (nt == 256) launch(k_p2g_f32<256>, 256); else launch(k_p2g_f32<512>, 512);
+    } else if (f32 && !global_atomics) {
+        if (surm == 2) MPM_LAUNCH_P2G_F32_NT(2); else if (surm == 1) MPM_LAUNCH_P2G_F32_NT(1); else MPM_LAUNCH_P2G_F32_NT(0);
     } else if (global_atomics) {
         if (surm == 2) MPM_LAUNCH_P2G_NT(true, 2); else if (surm == 1) MPM_LAUNCH_P2G_NT(true, 1); else MPM_LAUNCH_P2G_NT(true, 0);
     } else {
         if (surm == 2) MPM_LAUNCH_P2G_NT(false, 2); else if (surm == 1) MPM_LAUNCH_P2G_NT(false, 1); else MPM_LAUNCH_P2G_NT(false, 0);
     }
 #undef MPM_LAUNCH_P2G_NT
+#undef MPM_LAUNCH_P2G_F32_NT
 }
 
 void enqueue_materialize_map(hipStream_t st, const Launch& L, const Scenes& T, float* S, int64_t cap,

@@ -127,3 +127,35 @@ def test_fountain_frame_with_asflip_and_automatic_step(torch_cuda, oracle):
     print(f"[momentum] gpu={g_['P']} oracle={o_['P']} scale={scale:.3e}", flush=True)
     assert np.abs(g_["P"] - o_["P"]).max() <= 1e-2 * scale
     compare_totals(g_, o_, n, "fountain asflip auto-dt")
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("chunk", [64, 256, 512])
+def test_another_scenes_map_leaves_asflip_water_bit_for_bit(torch_cuda, mode, chunk):
+    """An ASFLIP scene's sums are rounded the same whatever map another scene of its context takes: the
+    water of a water and snow context with the learned (1) or closed-form (2) snow map against the same
+    with the exact map.  (Its scatter is exact, so nothing depends on the order of the adds.)"""
+    from paper_2111_00699_amd import mpm
+
+    water = scenes.nontrivial_state(scenes.jelly_cube(0)["x"], seed=5, kind="water")
+    snow = scenes.nontrivial_state(scenes.jelly_cube(0)["x"], seed=6, kind="snow")
+    print_case("asflip_beside_map", mode=mode, chunk=chunk)
+    sur = mpm.Surrogate()
+    sur.set(scenes.mlp_init(4), np.concatenate([np.zeros(12), np.ones(12)] * 2).astype(np.float32))
+    out = []
+    for m in (0, mode):
+        sim = mpm.Sim(64, 1e-4, scenes=[dict(n=64, dt=1e-4, bc="separate")] * 2, chunk=chunk)
+        sim.add_particles(scenes.WATER, water["x"], v=water["v"], C=water["C"], s=water["s"], scene=0)
+        sim.add_particles(scenes.SNOW, snow["x"], v=snow["v"], C=snow["C"], F=snow["F"], s=snow["s"], scene=1)
+        sim.set_transfer(FLIP, BMIN, BMAX, scene=0)
+        if m:
+            sim.use_surrogate(m, sur, tol=1e-2, dt_ref=1e-4, scene=1)
+        sim.substep(3)
+        stats = sim.stats()
+        assert stats["p2g_global_particles"] == 0
+        assert (stats["surrogate_particles"] + stats["surrogate_fallbacks"] > 0) == (m != 0)
+        out.append({k: t.cpu().numpy() for k, t in sim.read_particles(scene=0).items()})
+        sim.close()
+    for k in ("x", "v", "C", "s"):
+        assert np.array_equal(out[0][k], out[1][k]), k
+    sur.close()
