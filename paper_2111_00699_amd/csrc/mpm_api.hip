@@ -1388,7 +1388,10 @@ struct mpm_surrogate {
     float* v = nullptr;
     float* loss = nullptr;   // [loss_cap] per-step minibatch losses
     int loss_cap = 0;
-    void* work = nullptr;    // partial sums of the gradient or of the normalisation (sur_workspace_bytes)
+    // partial sums of the gradient or of the normalisation (sur_workspace_bytes): written and read by two
+    // launches, which threads that share the surrogate must not mix
+    void* work = nullptr;
+    std::mutex work_mutex;
     int step = 0;            // Adam steps taken
     unsigned long long* counter = nullptr;
 };
@@ -1488,17 +1491,22 @@ int mpm_surrogate_loss_grad(mpm_surrogate* s, int32_t precision, int64_t count, 
                             float* grad, float* loss) {
     if (!s || count < 1 || !X || !T || !grad || !loss || (precision != 0 && precision != 1))
         return sfail(s, MPM_EINVAL, "bad surrogate gradient arguments");
-    if (precision == MPM_SUR_BF16)
+    if (precision == MPM_SUR_BF16) {
+        std::lock_guard<std::mutex> lock(s->work_mutex);
         sur_grad16(s->stream, s->theta, s->norm, X, T, count, grad, loss, s->work);
-    else
+    } else {
         sur_grad_fp32(s->stream, s->theta, s->norm, X, T, count, grad, loss);
+    }
     SHIP_OK(hipGetLastError());
     return MPM_OK;
 }
 
 int mpm_surrogate_fit_norm(mpm_surrogate* s, int64_t count, const float* X, const float* T) {
     if (!s || count < 1 || !X || !T) return sfail(s, MPM_EINVAL, "bad normalisation arguments");
-    sur_norm(s->stream, X, T, count, s->norm, s->work);
+    {
+        std::lock_guard<std::mutex> lock(s->work_mutex);
+        sur_norm(s->stream, X, T, count, s->norm, s->work);
+    }
     SHIP_OK(hipGetLastError());
     return MPM_OK;
 }
@@ -1513,6 +1521,7 @@ namespace {
 int train_steps(mpm_surrogate* s, int64_t count, const float* X, const float* T, int32_t steps, int32_t batch,
                 float lr, uint64_t seed, float* loss_host, float* loss) {
     for (int k = 0; k < steps; ++k) {
+        std::lock_guard<std::mutex> lock(s->work_mutex);
         sur_train_step(s->stream, s->theta, s->norm, X, T, count, batch, seed, s->step, s->m, s->v, lr, loss + k, s->work);
         ++s->step;
     }

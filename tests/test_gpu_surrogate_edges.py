@@ -131,3 +131,45 @@ def test_normalisation_edges(torch_cuda, count):
     tol = 2.0 ** -22 * np.abs(want) + 2.0 ** -24
     for a in (got, off):
         assert np.all(np.abs(a - want) <= tol)
+
+
+def test_threads_share_a_surrogate(torch_cuda):
+    """Gradients asked for by several threads at once from one network: each gets its own rows' (the calls
+    enqueue on one stream, so nothing but their results can mix), bit for bit as when asked for alone."""
+    import ctypes as ct
+    import threading
+
+    from paper_2111_00699_amd import mpm
+
+    torch = torch_cuda
+    threads, calls, count = 4, 500, 64
+    sur = mpm.Surrogate()
+    sur.set(scenes.mlp_init(4), np.concatenate([np.zeros(12), np.ones(12)] * 2).astype(np.float32))
+    data = [[torch.from_numpy(a).cuda() for a in rows(count, 90 + k)] for k in range(threads)]
+    alone = [sur.loss_grad(X, T, precision=mpm.SUR_BF16) for X, T in data]
+    grad = torch.empty((threads, calls, mpm.SUR_PARAMS), dtype=torch.float32, device="cuda")
+    loss = torch.empty((threads, calls), dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    ptr = lambda t: ct.c_void_p(t.data_ptr())
+    bad = []
+
+    def work(k):
+        X, T = data[k]
+        args = [(sur.h, mpm.SUR_BF16, count, ptr(X), ptr(T), ptr(grad[k, i]), ptr(loss[k, i:])) for i in range(calls)]
+        start.wait()
+        for a in args:
+            if sur.lib.mpm_surrogate_loss_grad(*a) != mpm.OK:
+                bad.append(k)
+
+    start = threading.Barrier(threads)
+    pool = [threading.Thread(target=work, args=(k,)) for k in range(threads)]
+    for t in pool:
+        t.start()
+    for t in pool:
+        t.join()
+    sur.synchronize()
+    assert not bad
+    for k in range(threads):
+        wrong = (grad[k] != alone[k][1]).any(dim=1) | (loss[k] != alone[k][0])
+        assert int(wrong.sum()) == 0, (k, int(wrong.sum()))
+    sur.close()
