@@ -784,16 +784,18 @@ void enqueue_insert(hipStream_t st, float* S, int* ids, int64_t cap, int N0, int
                        F, s, ctl);
 }
 
-// Reads of at least this many positions sort each group by insertion id.  A particle's 25 values land 4
+// Reads of at least this many particles sort each group by insertion id.  A particle's 25 values land 4
 // bytes here and there: unsorted, a wave's store is 64 requests to the L2, whose rate bounds a large read.
 // Sorted, neighbours in a row of cells share theirs: 408 -> 234 us at 3.1M particles, 136 -> 90 at 1.39M, 21.8
 // -> 17.7 at 262K, the same 12.2 at 131K.  Below, one group's latency counts and the sort only adds to it:
-// 8.9 -> 9.5 us at 65K, 6.6 -> 8.2 at 30K.
+// 8.9 -> 9.5 us at 65K, 6.6 -> 8.2 at 30K.  Where most of the positions are other scenes' (storage order since
+// the last insertion), most groups would be sorted for nothing: a scene of 1,000 among 16.8M, 201 us sorted
+// and 47 us not.
 constexpr int READ_SORTED = 1 << 17;
 void enqueue_read(hipStream_t st, const Scenes& T, const float* S, const int* ids, int64_t cap, int j0, int n, int scene,
                   int Ns, int pending, float* x, float* v, float* C, float* F, float* s, const int* ctl, int* host_err) {
     const dim3 grid(cdiv(n > 0 ? n : 1, 8 * WG) * 8);
-    if (n >= READ_SORTED)
+    if (Ns >= READ_SORTED && 2 * (int64_t)Ns >= n)
         hipLaunchKernelGGL(k_read<true>, grid, dim3(WG), 0, st, S, ids, cap, j0, n, scene, Ns, pending, T, x, v, C, F, s, ctl,
                            host_err);
     else

@@ -100,3 +100,44 @@ def test_scene_reads_cover_their_storage(torch_cuda, sizes):
     sim.substep(1)
     check()
     sim.close()
+
+
+@pytest.mark.parametrize("sizes", [(131072, 131072), (131072, 131073), (300, 131072), (131071, 131073), (140000, 500000)])
+def test_scene_reads_before_the_first_rebuild(torch_cuda, sizes):
+    """Reads out of storage that holds other scenes too, at the sizes where the sort of a group begins (the
+    scene's particles, and their share of the positions)."""
+    print_case("unsorted_scene_reads", sizes=sizes)
+    sim = make_sim(torch_cuda, dict(n=64, dt=1e-5), num_scenes=2)
+    sts = [cloud(N, 420 + k, moving=True) for k, N in enumerate(sizes)]
+    for k, st in enumerate(sts):
+        add(sim, st, scene=k)
+    for k, st in enumerate(sts):
+        assert_same({f: t.cpu().numpy() for f, t in sim.read_particles(scene=k).items()}, st)
+    sim.close()
+
+
+def test_read_of_a_small_scene_costs_a_scan(torch_cuda):
+    """A scene of 1,000 particles among 16M that no rebuild has sorted: its read looks at one word per
+    position, 4 bytes against the 104 that the read of the 16M moves each way, and took 0.06 of that read's
+    time (0.27 when every group was sorted for it)."""
+    import time
+
+    torch, big = torch_cuda, 1 << 24
+    print_case("small_scene_read", big=big)
+    sim = make_sim(torch, dict(n=128, dt=1e-5), num_scenes=2, capacity=2 * big + 4096)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    for k, N in enumerate((big, 1000)):
+        sim.add_particles(scenes.WATER, 0.05 + 0.9 * torch.rand((3, N), device="cuda", generator=g), scene=k)
+    best = []
+    for k in range(2):
+        times = []
+        for _ in range(12):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            sim.read_particles(scene=k)
+            times.append(time.perf_counter() - t)
+        best.append(min(times))
+    sim.close()
+    print(f"[time] read of {big} {best[0] * 1e6:.0f} us, of 1000 {best[1] * 1e6:.0f} us", flush=True)
+    assert best[1] <= 0.15 * best[0]
