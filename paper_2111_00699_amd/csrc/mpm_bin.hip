@@ -208,11 +208,17 @@ __global__ __launch_bounds__(WG) void k_rs_scatter(const uint32_t* __restrict__ 
 }
 
 // --------------------------------------------------------- generic scan
-// Two launches: per-tile totals, and a per-tile exclusive scan that hands each
-// element its output offset; a workgroup of the second adds up the totals of
-// the tiles before its own (a few thousand at most, read coalesced), which a
-// launch of its own between the two did before.  op.limit(n): entries from
-// there on count nothing (workgroups past it leave at once).
+// Per-tile totals, then a per-tile exclusive scan that hands each element its
+// output offset.  Up to SCAN_DIRECT_TILES tiles a workgroup of the second adds
+// up the totals of the tiles before its own (read coalesced), which saves a
+// launch; those reads grow with the square of the tiles, so above that a launch
+// between the two scans the totals first (SCANNED).  The particles' block scan
+// that way and the other: 59.6 and 61.0 us at 12M particles (5.9K tiles), 80.5
+// and 79.8 at 16.7M, 970 and 531 at 130M; a rebuild of 500M takes 76.3 and 67.9
+// ms.
+// op.limit(n): entries from there on count nothing (workgroups past it leave at
+// once).
+constexpr int SCAN_DIRECT_TILES = 8192;
 template <int ITEMS, class Op>
 __global__ __launch_bounds__(WG) void k_scan_count(Op op, int n, int* __restrict__ tile_sums) {
     const int first = blockIdx.x * (WG * ITEMS) + threadIdx.x * ITEMS;
@@ -237,7 +243,35 @@ __device__ __forceinline__ int block_sum(const int* __restrict__ a, int n) {
     return tot;
 }
 
+// a[0 .. n) to its exclusive sums, in place, by one workgroup.
+__device__ __forceinline__ void scan_in_place(int* __restrict__ a, int n) {
+    constexpr int PER = 8;
+    int carry = 0;
+    for (int base = 0; base < n; base += WG * PER) {
+        const int first = base + threadIdx.x * PER;
+        int v[PER], s = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            v[i] = first + i < n ? a[first + i] : 0;
+            s += v[i];
+        }
+        int tot;
+        int off = carry + block_excl_scan(s, &tot);
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if (first + i < n) a[first + i] = off;
+            off += v[i];
+        }
+        carry += tot;
+    }
+}
+
 template <int ITEMS, class Op>
+__global__ __launch_bounds__(WG) void k_scan_top(Op op, int n, int* __restrict__ tile_sums) {
+    scan_in_place(tile_sums, (op.limit(n) + WG * ITEMS - 1) / (WG * ITEMS));
+}
+
+template <int ITEMS, bool SCANNED, class Op>
 __global__ __launch_bounds__(WG) void k_scan_emit(Op op, int n, const int* __restrict__ tile_sums,
                                                   int* __restrict__ total) {
     const int first = blockIdx.x * (WG * ITEMS) + threadIdx.x * ITEMS;
@@ -251,7 +285,7 @@ __global__ __launch_bounds__(WG) void k_scan_emit(Op op, int n, const int* __res
         c[i] = (first + i < n) ? op.count(first + i) : 0;
         s += c[i];
     }
-    const int before = block_sum(tile_sums, blockIdx.x);
+    const int before = SCANNED ? (n > 0 ? tile_sums[blockIdx.x] : 0) : block_sum(tile_sums, blockIdx.x);
     int tot;
     int off = before + block_excl_scan(s, &tot);
     if ((int)blockIdx.x == last && threadIdx.x == 0) *total = before + tot;
@@ -266,7 +300,12 @@ template <int ITEMS = SCAN_ITEMS, class Op>
 void device_scan(hipStream_t st, const Op& op, int n, int* tile_sums, int* total) {
     const int tiles = cdiv(n > 0 ? n : 1, WG * ITEMS);
     hipLaunchKernelGGL((k_scan_count<ITEMS, Op>), dim3(tiles), dim3(WG), 0, st, op, n, tile_sums);
-    hipLaunchKernelGGL((k_scan_emit<ITEMS, Op>), dim3(tiles), dim3(WG), 0, st, op, n, tile_sums, total);
+    if (tiles > SCAN_DIRECT_TILES) {
+        hipLaunchKernelGGL((k_scan_top<ITEMS, Op>), dim3(1), dim3(WG), 0, st, op, n, tile_sums);
+        hipLaunchKernelGGL((k_scan_emit<ITEMS, true, Op>), dim3(tiles), dim3(WG), 0, st, op, n, tile_sums, total);
+    } else {
+        hipLaunchKernelGGL((k_scan_emit<ITEMS, false, Op>), dim3(tiles), dim3(WG), 0, st, op, n, tile_sums, total);
+    }
 }
 
 struct OpHistScan {  // exclusive scan of the radix histogram in place
@@ -308,6 +347,12 @@ __global__ __launch_bounds__(WG) void k_blocks_count(const uint32_t* __restrict_
     }
 }
 
+// (a workgroup for the blocks' totals, one for the groups')
+__global__ __launch_bounds__(WG) void k_blocks_top(int tiles, int* __restrict__ sums) {
+    scan_in_place(sums + (int64_t)blockIdx.x * tiles, tiles);
+}
+
+template <bool SCANNED>
 __global__ __launch_bounds__(WG) void k_blocks_emit(const uint32_t* __restrict__ keys, int N, int pack, int tiles,
                                                     const int* __restrict__ sums, int* __restrict__ gstart,
                                                     uint32_t* __restrict__ gcode, int* __restrict__ group_start,
@@ -320,7 +365,8 @@ __global__ __launch_bounds__(WG) void k_blocks_emit(const uint32_t* __restrict__
         s0 += gb[i];
         s1 += gr[i];
     }
-    const int b0 = block_sum(sums, blockIdx.x), b1 = block_sum(sums + tiles, blockIdx.x);
+    const int b0 = SCANNED ? sums[blockIdx.x] : block_sum(sums, blockIdx.x);
+    const int b1 = SCANNED ? sums[tiles + blockIdx.x] : block_sum(sums + tiles, blockIdx.x);
     int t0, t1;
     int o0 = b0 + block_excl_scan(s0, &t0), o1 = b1 + block_excl_scan(s1, &t1);
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
@@ -758,8 +804,14 @@ void enqueue_rebuild(hipStream_t st, const Scenes& T, float* S_cur, float* S_alt
     // 3. geometric blocks with their merge groups, and work chunks
     const int stiles = cdiv(n1, SCAN_TILE);
     hipLaunchKernelGGL(k_blocks_count, dim3(stiles), dim3(WG), 0, st, B.keys[cur], N, pack, stiles, B.scan_tiles);
-    hipLaunchKernelGGL(k_blocks_emit, dim3(stiles), dim3(WG), 0, st, B.keys[cur], N, pack, stiles, B.scan_tiles, B.gstart,
-                       B.gcode, B.group_start, ctl);
+    if (stiles > SCAN_DIRECT_TILES) {
+        hipLaunchKernelGGL(k_blocks_top, dim3(2), dim3(WG), 0, st, stiles, B.scan_tiles);
+        hipLaunchKernelGGL(k_blocks_emit<true>, dim3(stiles), dim3(WG), 0, st, B.keys[cur], N, pack, stiles, B.scan_tiles,
+                           B.gstart, B.gcode, B.group_start, ctl);
+    } else {
+        hipLaunchKernelGGL(k_blocks_emit<false>, dim3(stiles), dim3(WG), 0, st, B.keys[cur], N, pack, stiles, B.scan_tiles,
+                           B.gstart, B.gcode, B.group_start, ctl);
+    }
     // (no more groups than particles, nor than slabs, or single blocks, of the padded dense grids)
     const int slabs = pack ? nbricks / 4 + 1 : nbricks;
     device_scan<1>(st, OpChunks{B.gstart, B.gcode, B.group_start, ctl, N, chunk, B.chunks, T}, N < slabs ? N : slabs,

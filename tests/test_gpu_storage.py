@@ -141,3 +141,56 @@ def test_read_of_a_small_scene_costs_a_scan(torch_cuda):
     sim.close()
     print(f"[time] read of {big} {best[0] * 1e6:.0f} us, of 1000 {best[1] * 1e6:.0f} us", flush=True)
     assert best[1] <= 0.15 * best[0]
+
+
+@pytest.mark.parametrize("N", [8192 * 2048, 8192 * 2048 + 1])
+def test_blocks_on_both_sides_of_the_scans_line(torch_cuda, N):
+    """From 8193 tiles of 2048 particles on, the block scan's totals are scanned by a launch of their own:
+    the blocks are those of the sorted codes, and the state comes back bit for bit."""
+    from paper_2111_00699_amd import mpm
+
+    torch = torch_cuda
+    print_case("scan_line_particles", N=N)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    x = 0.05 + 0.9 * torch.rand((3, N), device="cuda", generator=g)
+    sim = make_sim(torch, dict(n=256, dt=1e-5, gravity=(0, 0, 0)), capacity=N, flags=mpm.FLAG_ALLOC_EXACT)
+    sim.add_particles(REST, x)
+    sim.substep(1)
+    assert torch.equal(sim.read_particles()["x"], x)
+    keys, perm = sim.read_binning()
+    blocks = sim.read_blocks()
+    stats = sim.stats()
+    sim.close()
+    assert np.all(keys[1:] >= keys[:-1])
+    start = np.flatnonzero(np.concatenate([[True], keys[1:] >> 6 != keys[:-1] >> 6]))
+    assert np.array_equal(blocks["gstart"], start)
+    assert np.array_equal(blocks["gcode"], keys[start] >> 6)
+    assert np.array_equal(blocks["gcount"], np.diff(np.concatenate([start, [N]])))
+    assert np.array_equal(np.bincount(perm, minlength=N), np.ones(N, np.int64))
+    # (the chunks follow from the blocks: consecutive ones of a 2x2x1 slab, packed up to 256 particles)
+    assert stats["chunks"] >= N // 256 and stats["p2g_global_particles"] == 0
+
+
+def test_chunk_and_active_block_scans_above_the_line(torch_cuda, oracle):
+    """Eight scenes of 512^3 cells hold 17.6M blocks (8,582 tiles of 2048), and 2.2M particles may begin as
+    many chunks (8,594 tiles of 256): both scans take the launch for the totals."""
+    from paper_2111_00699_amd import mpm
+
+    per = 275000
+    print_case("scan_line_blocks", per=per)
+    sim = mpm.Sim(512, 1e-5, num_scenes=8, gravity=(0, 0, 0), capacity=8 * per, flags=mpm.FLAG_ALLOC_EXACT)
+    xs = [scenes.uniform(510 + k, 3 * per, 0, 0.05, 0.95).reshape(3, -1).astype(np.float32) for k in range(8)]
+    for k, x in enumerate(xs):
+        sim.add_particles(REST, x, scene=k)
+    sim.substep(1)
+    for k, x in enumerate(xs):
+        assert np.array_equal(sim.read_particles(scene=k)["x"].cpu().numpy(), x), k
+    for k in (0, 5, 7):
+        keys, perm = sim.read_binning(scene=k)
+        blocks = sim.read_blocks(scene=k)
+        ref = oracle.bin_particles(xs[k], 512)
+        for got, want in ((keys, "sorted"), (perm, "perm"), (blocks["gcode"], "gblock"), (blocks["gstart"], "gstart"),
+                          (blocks["gcount"], "gcount"), (blocks["active"], "pblock")):
+            assert np.array_equal(got, ref[want]), (k, want)
+    sim.close()
