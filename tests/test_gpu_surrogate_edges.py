@@ -133,6 +133,12 @@ def test_normalisation_edges(torch_cuda, count):
         assert np.all(np.abs(a - want) <= tol)
 
 
+@pytest.mark.parametrize("count", [4097, 16384, 16385])
+def test_normalisation_in_one_launch_and_in_two(torch_cuda, count):
+    """Up to 16,384 rows the columns are summed by the launch that stores the means."""
+    test_normalisation_edges(torch_cuda, count)
+
+
 def test_threads_share_a_surrogate(torch_cuda):
     """Gradients asked for by several threads at once from one network: each gets its own rows' (the calls
     enqueue on one stream, so nothing but their results can mix), bit for bit as when asked for alone."""
