@@ -450,7 +450,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
             for (int a = 0; a < 3; ++a) zone = zone && (unsigned)(st.base[a] - (4 * B[a] - 4)) <= (unsigned)(TILE - 3);
             in_zone = ok && zone;
             if constexpr (FUSED) {
-                left = left || !zone;
+                left = left || (ok && !zone);  // (a particle outside the grid stays where it is)
                 // A body that moves as one leaves its zone all at once, and the host sees the request some
                 // substeps late: a wave of every eighth chunk asks AHEAD substeps early (the cadence at which
                 // the host looks).  Sand of 3.1M, falling and splashing: 258.4 -> 252.5 us on average, the
@@ -464,7 +464,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
                         const float y = (x[a] + (AHEAD * dt) * v[a]) * P.fn - 0.5f - (float)(4 * B[a] - 4);
                         stays = stays && y >= 0.0f && y < (float)(TILE - 2);
                     }
-                    left = left || !stays;
+                    left = left || (ok && !stays);
                 }
             }
         } else {

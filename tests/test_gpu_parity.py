@@ -680,3 +680,20 @@ def test_fused_g2p_matches_separate_g2p_bit_for_bit(torch_cuda, kind):
     for k in ("x", "v", "C", "F", "s"):
         assert np.array_equal(a[0][k], b[0][k]), ("mid", k)
         assert np.array_equal(a[1][k], b[1][k]), ("end", k)
+
+
+@pytest.mark.parametrize("where", [(1.2, 0.5, 0.5), (0.5, -0.3, 0.5), (np.nan, 0.5, 0.5)])
+def test_lost_particles_ask_for_no_rebuilds(torch_cuda, where):
+    """A particle outside the grid takes no part in the transfer and does not move, so the sticky error
+    word is all it sets: a scene at rest beside it is sorted once, by the rebuild of its insertion."""
+    x = scenes.uniform(77, 3 * 3000, 0, 0.3, 0.6).reshape(3, -1).astype(np.float32)
+    x[:, 1234] = where
+    print_case("lost_particle", where=where)
+    sim = make_sim(torch_cuda, dict(n=64, dt=1e-5, gravity=(0.0, 0.0, 0.0)))
+    sim.add_particles(dict(scenes.JELLY, E=0.0), x)
+    sim.substep(100)
+    sim.synchronize()
+    stats = sim.stats(check=False)
+    sim.close()
+    assert stats["error"] != 0
+    assert stats["rebuilds"] == 1
