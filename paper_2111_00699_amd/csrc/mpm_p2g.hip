@@ -324,8 +324,10 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
     }
     unsigned err = 0;
     unsigned n_sur = 0, n_fb = 0;
-    // fused G2P: the free-zone request, as the G2P kernel makes it (the
-    // previous substep's P2G counted its tile fallbacks in the other slot)
+    // fused G2P: the free-zone request, made for particles that left and ahead
+    // for a body that is about to (below; the G2P kernel's own request comes
+    // after the exit only), and for tile fallbacks (the previous substep's P2G
+    // counted them in the other slot)
     bool left = FUSED && blockIdx.x == 0 && threadIdx.x == 0 && ctl[CTL_FB + (parity ^ 1)] > fb_limit;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     // this workgroup's slice of the staging buffer, filled front to back

@@ -131,3 +131,21 @@ def test_fountain_frame_totals(torch_cuda, oracle):
     # the water volume stays near its rest volume (weakly compressible)
     J = np.asarray(gs["s"], np.float64)
     assert abs(J.mean() - os_["s"].mean()) <= 1e-3
+
+
+def test_a_moving_body_is_sorted_before_it_leaves_its_zones(torch_cuda):
+    """The fused kernel asks for a rebuild four substeps before particles that move as one leave their free
+    zones; where the host looks after every substep (lag 1), none of them takes the global path."""
+    n, dt, cells, steps = 128, 1e-5, 0.3, 100
+    x = scenes.uniform(61, 3 * 100000, 0, 0.25, 0.5).reshape(3, -1).astype(np.float32)
+    v = np.zeros_like(x)
+    v[0] = cells / n / dt
+    print_case("moving_body", N=x.shape[1], cells=cells)
+    sim = make_sim(torch_cuda, dict(n=n, dt=dt, bc="separate", gravity=(0.0, 0.0, 0.0)), lag=1)
+    sim.add_particles(scenes.WATER, x, v=v)
+    sim.substep(steps)
+    stats = sim.stats()
+    sim.close()
+    assert stats["p2g_global_particles"] == 0
+    # sorted again at the soonest when the first may have moved 3 - 4 * 0.3 cells, 6 substeps after the last
+    assert 3 <= stats["rebuilds"] - 1 <= steps // 6
