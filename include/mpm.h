@@ -410,9 +410,8 @@ int mpm_surrogate_train(mpm_surrogate* s, int64_t count, const float* X_dev, con
  * mpm_surrogate_train allocates on demand -- in a fixed device array that the
  * library holds for the life of the process (one per device,
  * MPM_SUR_NOALLOC_MAX_STEPS 32-bit words, 16 KiB).  Arguments, results and
- * the synchronization at the
- * end are those of mpm_surrogate_train; the same seed gives the same
- * minibatches.  batch > MPM_SUR_NOALLOC_MAX_BATCH or steps >
+ * the synchronization at the end are those of mpm_surrogate_train; the same
+ * seed gives the same minibatches.  batch > MPM_SUR_NOALLOC_MAX_BATCH or steps >
  * MPM_SUR_NOALLOC_MAX_STEPS fails with MPM_EINVAL before anything is
  * enqueued.  Calls nothing that allocates (no hipMalloc, hipFree or
  * allocating library routine); the surrogate's parameters, Adam state and

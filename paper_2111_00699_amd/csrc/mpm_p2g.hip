@@ -82,10 +82,12 @@ constexpr double DENORM_SPLIT = 0x1p-1000;  // the weights' share of the scale i
 // has a light weight (59% of the waves), but only a node at the very edge of a
 // chunk's material has no other contribution: without light particles no node
 // is weak, with the usual four of a chunk few are (runs of 32K to 3.1M
-// particles take 0.1% to 0.5% longer than with a bound of 2^-32 for any L,
-// which left equal terms' roundings at up to 9e-5 of a node's mass).
+// particles take 0.0% to 0.5% longer than with one unit added to every term
+// and a bound of 2^-32 for any L, which left equal terms' roundings at up to
+// 9e-5 of a node's mass).
 // One particle in 4 10^4 has a weight that may round to nothing: it adds one
-// unit more to its nodes, so that a node that only such weights reach shows.
+// unit more to its nodes, so that a node that only such weights reach shows
+// (were all L such particles, 2^-21 of the sum).
 constexpr float LIGHT_W = 0x1.01p-32f;  // (with room for the rounding of a product of FP32 weights)
 constexpr int WEAK_SHIFT = FRAC_W - 33;
 
@@ -480,6 +482,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
         float m_bound = 0.0f;  // K, above every |m| of the chunk
         int em = 0;            // 27/64 (m + K) < 2^em: momentum units are 2^(em - FRAC_M)
         int copies = 1;        // of the tile, an odd number of nodes apart (different banks)
+        float wmin = 1.0f;     // the smallest weight of the particle's stencil
         int lights = 0;        // the chunk's particles with a weight below LIGHT_W
         // the smallest of a stencil's 27 weights is the product of its per-axis minima
         auto smallest_weight = [&] {
@@ -507,7 +510,10 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
             }
             const int mbw = wave_max(__float_as_int(mb));
             int light_w = 0;
-            if constexpr (!F32) light_w = (int)__popcll(__ballot(in_tile && smallest_weight() < LIGHT_W));
+            if constexpr (!F32) {
+                wmin = smallest_weight();
+                light_w = (int)__popcll(__ballot(in_tile && wmin < LIGHT_W));
+            }
             if (lane == 0) {
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
@@ -655,7 +661,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
             double wx[3], wy[3], wz[3], ax[3], ay[3], az[3], mz[3];
             const float ms = ldexpf(1.0f, FRAC_M - 74 - em);  // 2^(FRAC_M - em - 1074) / DENORM_SPLIT
             const double k = (double)m_bound * (double)ms;
-            const double mark = smallest_weight() <= 0x1p-54f ? 0x1p-1074 : 0.0;  // (one unit)
+            const double mark = wmin <= 0x1p-54f ? 0x1p-1074 : 0.0;  // (one unit)
 #pragma unroll
             for (int o = 0; o < 3; ++o) {
                 wx[o] = (double)st.w[0][o];
@@ -748,7 +754,7 @@ __device__ __forceinline__ void p2g_body(float* __restrict__ S, int64_t cap_, co
                 // lanes of a wave.  The wave takes such particles one by one and tests 64 weak nodes at a
                 // time, a lane each.
                 const float bound = (float)lights * (0.5f * LIGHT_W);
-                const unsigned long long tiny = __ballot(tiled && smallest_weight() < bound);
+                const unsigned long long tiny = __ballot(tiled && wmin < bound);
                 for (int k0 = 0; tiny && k0 < nw; k0 += 64) {
                     const bool mine = k0 + lane < nw;
                     const int e = mine ? weak[k0 + lane] : 0, wx = e & 31, wy = (e >> 5) & 31, wz = e >> 10;
